@@ -38,7 +38,8 @@
 // without leaving registers.  A contraction over ROWS needs each lane to hold 8
 // rows of one column; multiplying a row fragment by a 0/1 selection matrix on
 // the matrix core (exact) gives lane (i, g) rows 4g..4g+3 of column i, and two
-// sub-tiles give the 8 rows.
+// sub-tiles give the 8 rows.  fp32 storage, whose 16x16x4 products make that the
+// larger part of the work, reads columns from a per-wave LDS tile instead.
 //
 // Feature maps (template parameter PHI): elu(x) + 1 (Eq. (3) as read from the
 // linear-transformer paper that Sec. 3.2 cites), or ReLU with phi'(0) = 0 (the
@@ -56,11 +57,11 @@ namespace sla {
 
 // ------------------------------------------------------------------ forward
 template <typename T, int D, int PHI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWpe<T, SLA_FWD_WPE>)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SLA_FWD_WPE)))
 void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
                const T* __restrict__ v, T* __restrict__ o) {
-  constexpr int KT = kStateTiles<D>;
-  __shared__ floatx4 s_part[kWaves * KT * 64];  // partial states of a long window
+  constexpr int SL = kSlot<T, D>;
+  __shared__ floatx4 s_part[kWaves * SL];        // partial states of a long window; fp32: staging tiles
   __shared__ WaveMeta s_meta[kWaves];            // the items ahead (perm slices, offsets, entries)
   const int lane = lane_id();
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -75,6 +76,8 @@ void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
   const T* const mats[3] = {k, v, q};
   constexpr unsigned kKV = 3u, kQ = 4u, kAll = 7u;
 
+  floatx4* const slot = s_part + wv * SL;
+  float* const stage = reinterpret_cast<float*>(slot);   // fp32 only
   WaveMeta& meta = s_meta[wv];
   const bool csr = perm == nullptr;
   int32_t item = blockIdx.x;
@@ -128,13 +131,14 @@ void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
 #pragma unroll
         for (int jj = 0; jj < kBlockJobs; ++jj) {
           const int32_t r0 = base + kSliceRows * jj;
-          if (job_overlaps(r0, wa, wb)) state_seg<T, D, 3, PHI>(bk.j[jj], r0, wa, wb, i, g, sel, st);
+          if (job_overlaps(r0, wa, wb)) state_seg<T, D, 3, PHI>(bk.j[jj], r0, wa, wb, i, g, sel, st, stage);
         }
       }
+      state_finish<T, D>(st);
       if (wi.shared) {
-        publish<D>(st, s_part + wv * KT * 64, lane);
+        publish<D>(st, slot, lane);
         lds_barrier();
-        combine<D>(st, s_part, lane, wv, ww.pair);
+        combine<D, SL>(st, s_part, lane, wv, ww.pair);
         lds_barrier();  // the slots may be written by the next long item
       }
       FwdOp<T, D> op;
@@ -164,13 +168,17 @@ void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
 // Per window: state S, z from K, V; then dq and the state gradients from Q, dout;
 // then dk, dv from K, V (held in registers since the first phase).
 template <typename T, int D, int PHI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWpe<T, SLA_BWD_WPE>)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SLA_BWD_WPE)))
 void k_sla_bwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
                const T* __restrict__ v, const T* __restrict__ dout, T* __restrict__ dq,
                T* __restrict__ dk, T* __restrict__ dv) {
-  constexpr int KT = kStateTiles<D>;
-  __shared__ floatx4 s_part[2][kWaves * KT * 64];  // partial S, z / dS, dz of a long window
-  __shared__ float s_tr[kWaves][D * kTrLd<D>];     // transposes, one tile per wave
+  constexpr int SL = kSlot<T, D>;
+  constexpr bool NW = Ty<T>::kNarrow;
+  // partial S, z / dS, dz of a long window, and a tile per wave for transposes.  fp32
+  // keeps both over the wave's staging tile (43 instead of 92 KB, so that LDS
+  // allows three workgroups per CU): one slot set, with a barrier after its readers
+  __shared__ floatx4 s_part[NW ? 2 : 1][kWaves * SL];
+  __shared__ float s_tr[NW ? kWaves : 1][NW ? D * kTrLd<D> : 1];
   __shared__ WaveMeta s_meta[kWaves];              // the items ahead (perm slices, offsets, entries)
   const int lane = lane_id();
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -182,7 +190,8 @@ void k_sla_bwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
   const size_t rs = (size_t)a.H * D;
   const int32_t n = a.n, G = gridDim.x;
   const Sel<T, D> sel(i, g);
-  float* tile = s_tr[wv];
+  float* const stage = reinterpret_cast<float*>(s_part[0] + wv * SL);   // fp32 only
+  float* const tile = NW ? s_tr[NW ? wv : 0] : stage;
   const T* const mats[4] = {k, v, q, dout};
   constexpr unsigned kKV = 3u, kQD = 12u, kAll = 15u;
 
@@ -238,13 +247,15 @@ void k_sla_bwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
 #pragma unroll
         for (int jj = 0; jj < kBlockJobs; ++jj) {
           const int32_t r0 = base + kSliceRows * jj;
-          if (job_overlaps(r0, wa, wb)) state_seg<T, D, 4, PHI>(bk.j[jj], r0, wa, wb, i, g, sel, st);
+          if (job_overlaps(r0, wa, wb)) state_seg<T, D, 4, PHI>(bk.j[jj], r0, wa, wb, i, g, sel, st, stage);
         }
       }
+      state_finish<T, D>(st);
       if (wi.shared) {
-        publish<D>(st, s_part[0] + wv * KT * 64, lane);
+        publish<D>(st, s_part[0] + wv * SL, lane);
         lds_barrier();
-        combine<D>(st, s_part[0], lane, wv, ww.pair);
+        combine<D, SL>(st, s_part[0], lane, wv, ww.pair);
+        if constexpr (!NW) lds_barrier();   // the slots are written again by make_state_op
       }
       make_state_op<T, D, PHI>(st, op, tile, i, g, a.eps);
       // phase 1: dq and beta dS, beta dz
@@ -260,15 +271,17 @@ void k_sla_bwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
         for (int jj = 0; jj < kBlockJobs; ++jj) {
           const int32_t r0 = base + kSliceRows * jj;
           if (job_overlaps(r0, wa, wb))
-            qgrad_seg<T, D, 4, 2, 3, PHI>(bk.j[jj], r0, wa, wb, i, g, sel, op, dq, rs, col, st);
+            qgrad_seg<T, D, 4, 2, 3, PHI>(bk.j[jj], r0, wa, wb, i, g, sel, op, dq, rs, col, st, stage);
         }
       }
+      state_finish<T, D>(st);
       if (wi.shared) {
         // slot set 1 is free: its last readers passed the barrier above before
         // this item's set-0 reads ended (sets alternate within every long item)
-        publish<D>(st, s_part[1] + wv * KT * 64, lane);
+        publish<D>(st, s_part[NW ? 1 : 0] + wv * SL, lane);
         lds_barrier();
-        combine<D>(st, s_part[1], lane, wv, ww.pair);
+        combine<D, SL>(st, s_part[NW ? 1 : 0], lane, wv, ww.pair);
+        if constexpr (!NW) lds_barrier();
       }
       make_grad_op<T, D>(st, op.inv_beta, op, tile, i, g);
       // phase 2: dk, dv

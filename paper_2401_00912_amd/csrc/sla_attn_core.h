@@ -419,14 +419,101 @@ __device__ __forceinline__ bool sub_overlaps(int32_t r0, int s, int32_t a, int32
   return r0 + 16 * s < b && r0 + 16 * s + 16 > a;
 }
 
+// ------------------------------------------------- fp32 contractions over rows
+// fp32 storage: a selection product would cost eight 16x16x4 products per 16-row
+// tile, more than the contraction itself.  A wave stages the rows of a job in its
+// own LDS tile instead (row fragments out as 16-byte pieces) and reads them back
+// by columns: lane (i, g) of a 16x16x4 product holds row 4 k + g, column i, for A
+// and B alike, and groups of four rows outside the window are skipped.  The
+// extra column (sums over rows) stays on the vector units: every lane adds its
+// rows' slots, and state_finish sums the 16 lanes of a lane group once per window.
+// On a Waymo-like frame (60k rows, H = 4, d = 32) against selection products:
+// forward 47 us against 65, backward 83 against 151 (2 waves per SIMD against 1),
+// the relative error of dq against float64 3.2e-7 against 3.7e-7.
+template <int D>
+constexpr int kStageLd = D + 4;   // 16-byte aligned rows; 4-byte column reads without bank conflicts
+// a matrix of a job, and a wave's tile (two matrices), in floats
+template <int D>
+constexpr int kStageMat = kSliceRows * kStageLd<D>;
+template <int D>
+constexpr int kStageWave = 2 * kStageMat<D>;
+
+template <int D>
+__device__ __forceinline__ void stage_put(float* mat, int s, int i, int g, const Raw<float, Geo<D>::KS>& x) {
+#pragma unroll
+  for (int t = 0; t < Geo<D>::NT; ++t)
+    *reinterpret_cast<float4*>(mat + (16 * s + i) * kStageLd<D> + 16 * t + 4 * g) =
+        make_float4(x[4 * t], x[4 * t + 1], x[4 * t + 2], x[4 * t + 3]);
+}
+
+// M += X^T Y over the rows [a, b) of a staged job (rows r0 .. r0 + 31).
+template <int D>
+__device__ __forceinline__ void stage_product(const float* X, const float* Y, int32_t r0, int32_t a, int32_t b,
+                                              int i, int g, State<D>& st) {
+  constexpr int NT = Geo<D>::NT;
+#pragma unroll
+  for (int k = 0; k < kSliceRows / 4; ++k) {
+    if (r0 + 4 * k >= b || r0 + 4 * k + 4 <= a) continue;
+    float x[NT], y[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      x[t] = X[(4 * k + g) * kStageLd<D> + 16 * t + i];
+      y[t] = Y[(4 * k + g) * kStageLd<D> + 16 * t + i];
+    }
+#pragma unroll
+    for (int et = 0; et < NT; ++et)
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct)
+        st.M[et][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[et], y[ct], st.M[et][ct], 0, 0, 0);
+  }
+}
+
+// Sum over the 16 lanes of a lane group, in every lane (DPP row rotations).
+__device__ __forceinline__ float sum_rows16(float x) {
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false));  // row_ror:8
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, false));  // row_ror:4
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x122, 0xf, 0xf, false));  // row_ror:2
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x121, 0xf, 0xf, false));  // row_ror:1
+  return x;
+}
+
+// The extra column of a window's accumulated state (fp32: lanes to rows' sums).
+template <typename T, int D>
+__device__ __forceinline__ void state_finish(State<D>& st) {
+  if constexpr (!Ty<T>::kNarrow) {
+#pragma unroll
+    for (int t = 0; t < Geo<D>::NT; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) st.V[t][j] = sum_rows16(st.V[t][j]);
+  }
+}
+
 // Rows [a, b) of one slice into the state: M += phi(K)^T V, V += phi(K)^T 1.
-// K is matrix 0, V matrix 1.
+// K is matrix 0, V matrix 1.  fp32: `stage` is the wave's LDS tile.
 template <typename T, int D, int NM, int PHI>
 __device__ __forceinline__ void state_seg(const Slice<T, Geo<D>::KS, NM>& sb, int32_t r0,
                                           int32_t a, int32_t b, int i, int g,
-                                          const Sel<T, D>& sel, State<D>& st) {
+                                          const Sel<T, D>& sel, State<D>& st, float* stage = nullptr) {
   constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
   using F = Frag<T, KS>;
+  if constexpr (!Ty<T>::kNarrow) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if (!sub_overlaps(r0, s, a, b)) continue;
+      const int32_t row = r0 + 16 * s + i;
+      const bool in = sb.ok[s] && row >= a && row < b;
+      const Raw<T, KS> fk = phi_frag<T, KS, PHI>(sb.x[0][s], in);
+      const Raw<T, KS> vv = in ? sb.x[1][s] : F::zero();
+#pragma unroll
+      for (int r = 0; r < KS; ++r) st.V[r >> 2][r & 3] += fk[r];
+      stage_put<D>(stage, s, i, g, fk);
+      stage_put<D>(stage + kStageMat<D>, s, i, g, vv);
+    }
+    wave_lds_sync();
+    stage_product<D>(stage, stage + kStageMat<D>, r0, a, b, i, g, st);
+    wave_lds_sync();   // the tile may be written again
+    return;
+  } else {
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
   Raw<T, KS> fk[2], vv[2];
 #pragma unroll
@@ -453,6 +540,7 @@ __device__ __forceinline__ void state_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) st.M[et][ct] = Frag<T, 8>::mma(pk, pv[ct], st.M[et][ct]);
   }
+  }
 }
 
 // Operand of a head-dim contraction from result tiles: slot r of lane (i, g) is
@@ -473,6 +561,7 @@ struct FwdOp {
   Raw<T, Geo<D>::KS> A[Geo<D>::NT];  // sig S as operand of result tile ct (contract e)
   Raw<T, Geo<D>::KS> Az;             // sig z in rows 0, 4, 8, 12: the normaliser of every
                                      // row lands in component 0 of every lane group
+                                     // (fp32: z itself, slot r of lane group g = z[E(g, r)])
   float seps;                        // sig eps
 };
 
@@ -488,12 +577,27 @@ __device__ __forceinline__ void make_fwd_op(const State<D>& st, FwdOp<T, D>& op,
     for (int et = 0; et < NT; ++et) col[et] = st.M[et][ct];
     op.A[ct] = tiles_operand<T, D>(col, sig);
   }
-  const float zmul = (i & 3) == 0 ? sig : 0.f;
+  const float zmul = !Ty<T>::kNarrow ? 1.f : ((i & 3) == 0 ? sig : 0.f);
   float zx[KS];
 #pragma unroll
   for (int r = 0; r < KS; ++r) zx[r] = st.V[r >> 2][r & 3] * zmul;
   op.Az = Frag<T, KS>::from_f32(zx);
   op.seps = sig * eps;
+}
+
+// phi(q) . z of the row of each lane: from the matrix cores (az: sig z in rows 0,
+// 4, 8, 12), in fp32 from the vector units (az: z by slots).
+template <typename T, int D>
+__device__ __forceinline__ float normaliser(const Raw<T, Geo<D>::KS>& az, const Raw<T, Geo<D>::KS>& bq) {
+  if constexpr (Ty<T>::kNarrow) {
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    return Frag<T, Geo<D>::KS>::mma(az, bq, zero)[0];
+  } else {
+    float x = 0.f;
+#pragma unroll
+    for (int r = 0; r < Geo<D>::KS; ++r) x += az[r] * bq[r];
+    return sum_groups(x);
+  }
 }
 
 // o = phi(q) S / (phi(q) . z + eps) for rows [a, b) of one slice (Q is matrix
@@ -512,8 +616,7 @@ __device__ __forceinline__ void apply_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
     const int32_t row = r0 + 16 * s + i;
     const bool in = sb.ok[s] && row >= a && row < b;
     const Raw<T, KS> bq = phi_frag<T, KS, PHI>(sb.x[QM][s], in);
-    const floatx4 den = F::mma(op.Az, bq, zero);
-    const float scale = recip<T>(den[0] + op.seps);
+    const float scale = recip<T>(normaliser<T, D>(op.Az, bq) + op.seps);
     float ox[KS];
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) {
@@ -525,17 +628,14 @@ __device__ __forceinline__ void apply_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
   }
 }
 
-// Target occupancy (waves per SIMD) handed to the register allocator.
+// Target occupancy (waves per SIMD) handed to the register allocator; every storage
+// type and head_dim reaches it without spilling vector registers.
 #ifndef SLA_FWD_WPE
 #define SLA_FWD_WPE 3
 #endif
 #ifndef SLA_BWD_WPE
 #define SLA_BWD_WPE 2
 #endif
-// fp32 storage doubles the resident rows: ask for half the occupancy
-template <typename T, int W16>
-constexpr int kWpe = sizeof(T) == 4 ? (W16 > 2 ? W16 / 2 : 1) : W16;
-
 // ----------------------------------------------------------- backward math
 // bf16 keeps 8 significant bits, so the backward carries the operands of its
 // cancelling differences as a sum of two bf16 values (high part and rounding
@@ -553,7 +653,7 @@ template <typename T, int D>
 struct BwdOp {
   Raw<T, Geo<D>::KS> A[Geo<D>::NT];  // unused                           | rho dS^T (dfk = v dS^T, tile et)
   Raw<T, Geo<D>::KS> B[Geo<D>::NT];  // sig S^T (dfq = dout S^T, tile et) | rho dS  (dv = phi(k) dS, tile ct)
-  Raw<T, Geo<D>::KS> Az;             // sig z in rows 0, 4, 8, 12 (normaliser) | unused
+  Raw<T, Geo<D>::KS> Az;             // sig z in rows 0, 4, 8, 12 (normaliser; fp32: z by slots) | unused
   float z[Geo<D>::KS];               // sig z (as rounded in Az + Azl)    | dz
   float inv_scale;                   // unused                            | 1 / rho
   float bsig;                        // beta sig: phi(q) / den in the state gradients is
@@ -636,7 +736,7 @@ __device__ __forceinline__ void make_state_op(const State<D>& st, BwdOp<T, D>& o
       zl[r] = (i & 3) == 0 ? lo : 0.f;
     }
     op.z[r] = zs;
-    zx[r] = (i & 3) == 0 ? zh : 0.f;
+    zx[r] = !Ty<T>::kNarrow || (i & 3) == 0 ? zh : 0.f;
   }
   op.Az = Frag<T, KS>::from_f32(zx);
   if constexpr (kSplitGrad<T>) op.Azl = Frag<T, KS>::from_f32(zl);
@@ -676,7 +776,7 @@ template <typename T, int D, int NM, int QI, int DI, int PHI>
 __device__ __forceinline__ void qgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, int32_t r0,
                                           int32_t a, int32_t b, int i, int g,
                                           const Sel<T, D>& sel, const BwdOp<T, D>& op, T* dq,
-                                          size_t rs, int col, State<D>& gs) {
+                                          size_t rs, int col, State<D>& gs, float* stage) {
   constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
   using F = Frag<T, KS>;
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -695,9 +795,10 @@ __device__ __forceinline__ void qgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
     float dphq[KS], fq[KS];
     phi_dphi<T, KS, PHI>(sb.x[QI][s], in, bq, dphq);
     F::to_f32(bq, fq);
-    floatx4 den4 = F::mma(op.Az, bq, zero);
-    if constexpr (SP) den4 = F::mma(op.Azl, bq, den4);
-    const float rden = recip<T>(in ? den4[0] + op.seps : 1.f);
+    float den;
+    if constexpr (SP) den = F::mma(op.Azl, bq, F::mma(op.Az, bq, zero))[0];
+    else den = normaliser<T, D>(op.Az, bq);
+    const float rden = recip<T>(in ? den + op.seps : 1.f);
     // dfq = sig dout S^T; dout.o = phi(q) S dout^T / den = phi(q).dfq / den'
     floatx4 dfq[NT];
     float dot = 0.f;
@@ -726,6 +827,13 @@ __device__ __forceinline__ void qgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
       xs[r] = (PHI != kPhiRelu || op.z[r] > 0.f) ? fq[r] * w : 0.f;
       ns[r] = -dot;
     }
+    if constexpr (!Ty<T>::kNarrow) {
+#pragma unroll
+      for (int r = 0; r < KS; ++r) gs.V[r >> 2][r & 3] -= xs[r] * dot;
+      stage_put<D>(stage, s, i, g, F::from_f32(xs));
+      stage_put<D>(stage + kStageMat<D>, s, i, g, dr[s]);
+      continue;
+    }
     xr[s] = F::from_f32(xs);
     nd[s] = F::from_f32(ns);
     if constexpr (SP) {
@@ -735,6 +843,12 @@ __device__ __forceinline__ void qgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
       nl[s] = F::from_f32(ns);
     }
   }
+  if constexpr (!Ty<T>::kNarrow) {
+    wave_lds_sync();
+    stage_product<D>(stage, stage + kStageMat<D>, r0, a, b, i, g, gs);
+    wave_lds_sync();   // the tile may be written again
+    return;
+  } else {
   // the row transposes, each packed into an operand as soon as it is formed (the
   // packed operand takes half the registers of its two result tiles)
   auto rows_of = [&](const Raw<T, KS>(&x)[2], int t) -> Raw<T, 8> {
@@ -753,6 +867,7 @@ __device__ __forceinline__ void qgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
     if constexpr (SP) gs.V[et] = Frag<T, 8>::mma(px, pl, gs.V[et]);
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) gs.M[et][ct] = Frag<T, 8>::mma(px, pd[ct], gs.M[et][ct]);
+  }
   }
 }
 
@@ -1171,16 +1286,21 @@ __device__ __forceinline__ void publish(const State<D>& st, floatx4* slot, int l
   for (int a = 0; a < NT; ++a) slot[(t++) * 64 + lane] = st.V[a];
 }
 
-// st = sum of the published states of the waves that share this wave's long
-// window (all four, or the pair 2m, 2m + 1), in wave order.
-template <int D>
+// A wave's slot: its published state, in fp32 placed over its staging tile.
+template <typename T, int D>
+constexpr int kSlot = Ty<T>::kNarrow ? kStateTiles<D> * 64 : kStageWave<D> / 4;
+static_assert(kSlot<float, 32> >= kStateTiles<32> * 64 && kSlot<float, 16> >= kStateTiles<16> * 64, "slot");
+
+// st = sum of the published states (SL floatx4 apart) of the waves that share
+// this wave's long window (all four, or the pair 2m, 2m + 1), in wave order.
+template <int D, int SL>
 __device__ __forceinline__ void combine(State<D>& st, const floatx4* slots, int lane, int wv,
                                         bool pair) {
-  constexpr int NT = Geo<D>::NT, KT = kStateTiles<D>;
+  constexpr int NT = Geo<D>::NT;
   st.clear();
   const int w0 = pair ? (wv & ~1) : 0, nw = pair ? 2 : kWaves;
   for (int w = w0; w < w0 + nw; ++w) {
-    const floatx4* sl = slots + w * KT * 64;
+    const floatx4* sl = slots + w * SL;
     int t = 0;
 #pragma unroll
     for (int a = 0; a < NT; ++a)

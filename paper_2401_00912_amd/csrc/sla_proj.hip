@@ -358,7 +358,7 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
         if (wi.shared) {
           publish<D>(st, s_part + wv * KT * 64, lane);
           lds_barrier();
-          combine<D>(st, s_part, lane, wv, ww.pair);
+          combine<D, kSlot<T, D>>(st, s_part, lane, wv, ww.pair);
           lds_barrier();  // the slots may be written by the next long item
         }
         FwdOp<T, D> op;
@@ -383,7 +383,7 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
         if (wi.shared) {
           publish<D>(st, s_part + wv * KT * 64, lane);
           lds_barrier();
-          combine<D>(st, s_part, lane, wv, ww.pair);
+          combine<D, kSlot<T, D>>(st, s_part, lane, wv, ww.pair);
           lds_barrier();
         }
         FwdOp<T, D> op;
