@@ -55,8 +55,10 @@
 
 namespace sla {
 
+constexpr int kPartFill = 100;   // parts fill the grid at most once
+
 // ------------------------------------------------------------------ forward
-template <typename T, int D, int PHI>
+template <typename T, int D, int PHI, bool PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SLA_FWD_WPE)))
 void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
                const T* __restrict__ v, T* __restrict__ o) {
@@ -67,7 +69,7 @@ void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const PlanHeader* hdr = a.hdr;
   if (hdr->magic != kPlanMagic || hdr->n != a.n || hdr->num_windows != a.W) return;
-  const Items it = work_items(a, hdr);
+  const Items it = work_items<PARTS ? kPartFill : 0>(a, hdr);
   const int32_t* perm = hdr->csr ? nullptr : a.perm;
   const int i = lane & 15, g = lane >> 4;
   const size_t rs = (size_t)a.H * D;
@@ -104,7 +106,7 @@ void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
     BlockRows br;
     block_rows_lds(br, ww, meta.perm[par], csr, lane);
     Stream str;
-    stream_lds(str, ww, a, meta.offs[par], lane);
+    stream_lds(str, ww, a, it, meta.offs[par], lane);
     const WaveWork wnn = decode_work(a, item_slot(it, item + 2 * G, wv), lds_entry(&meta.ent[par]), wv);
     wait_lgkm();
     // requests ahead: the slice of the item after next, the next item's windows,
@@ -113,7 +115,9 @@ void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
     request_offs(wn, a, meta.offs[par ^ 1], lane);
     request_entry(a, item_slot(it, item + 3 * G, wv), &meta.ent[par ^ 1], lane);
     Block<T, D, 3> bk;
-    if (ww.kind != 0) block_fetch<T, D, 3>(bk, br, ww.ra, ww.rb, n, mats, first, rs, col, g);
+    int32_t fa = INT32_MIN, fb = ww.rb;   // the rows of this item's windows
+    if constexpr (PARTS) str.rows(fa, fb);
+    if (ww.kind != 0) block_fetch<T, D, 3>(bk, br, ww.ra, fb, n, mats, first, rs, col, g, fa);
 
     block_arrange<T, D, 3>(bk, first);
     WinIter wi;
@@ -167,7 +171,7 @@ void k_sla_fwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
 // ----------------------------------------------------------------- backward
 // Per window: state S, z from K, V; then dq and the state gradients from Q, dout;
 // then dk, dv from K, V (held in registers since the first phase).
-template <typename T, int D, int PHI>
+template <typename T, int D, int PHI, bool PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SLA_BWD_WPE)))
 void k_sla_bwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
                const T* __restrict__ v, const T* __restrict__ dout, T* __restrict__ dq,
@@ -184,7 +188,7 @@ void k_sla_bwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const PlanHeader* hdr = a.hdr;
   if (hdr->magic != kPlanMagic || hdr->n != a.n || hdr->num_windows != a.W) return;
-  const Items it = work_items(a, hdr);
+  const Items it = work_items<PARTS ? kPartFill : 0>(a, hdr);
   const int32_t* perm = hdr->csr ? nullptr : a.perm;
   const int i = lane & 15, g = lane >> 4;
   const size_t rs = (size_t)a.H * D;
@@ -219,7 +223,7 @@ void k_sla_bwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
     BlockRows br;
     block_rows_lds(br, ww, meta.perm[par], csr, lane);
     Stream str;
-    stream_lds(str, ww, a, meta.offs[par], lane);
+    stream_lds(str, ww, a, it, meta.offs[par], lane);
     const WaveWork wnn = decode_work(a, item_slot(it, item + 2 * G, wv), lds_entry(&meta.ent[par]), wv);
     wait_lgkm();
     // requests ahead (see the forward); then this item's rows
@@ -227,7 +231,9 @@ void k_sla_bwd(KernelArgs a, const T* __restrict__ q, const T* __restrict__ k,
     request_offs(wn, a, meta.offs[par ^ 1], lane);
     request_entry(a, item_slot(it, item + 3 * G, wv), &meta.ent[par ^ 1], lane);
     Block<T, D, 4> bk;
-    if (ww.kind != 0) block_fetch<T, D, 4>(bk, br, ww.ra, ww.rb, n, mats, first, rs, col, g);
+    int32_t fa = INT32_MIN, fb = ww.rb;   // the rows of this item's windows
+    if constexpr (PARTS) str.rows(fa, fb);
+    if (ww.kind != 0) block_fetch<T, D, 4>(bk, br, ww.ra, fb, n, mats, first, rs, col, g, fa);
 
     block_arrange<T, D, 4>(bk, first);
     WinIter wi;
@@ -312,10 +318,10 @@ static hipError_t fwd_impl(const void* plan, int32_t n, int32_t W, int32_t H, fl
                            hipStream_t stream) {
   const PlanLayout lay = plan_layout(n, W);
   const KernelArgs a = kernel_args(plan, lay, n, W, H, eps);
-  const void* kern = reinterpret_cast<const void*>(&k_sla_fwd<T, D, PHI>);
-  hipLaunchKernelGGL((k_sla_fwd<T, D, PHI>), dim3(grid_size(kern, lay, n, H)), dim3(64 * kWaves), 0,
-                     stream, a, static_cast<const T*>(q), static_cast<const T*>(k),
-                     static_cast<const T*>(v), static_cast<T*>(o));
+  const int grid = grid_size(reinterpret_cast<const void*>(&k_sla_fwd<T, D, PHI, false>), lay, n, H);
+  const auto kern = parts_fit(grid, n, H, kPartFill) ? &k_sla_fwd<T, D, PHI, true> : &k_sla_fwd<T, D, PHI, false>;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a, static_cast<const T*>(q),
+                     static_cast<const T*>(k), static_cast<const T*>(v), static_cast<T*>(o));
   return hipGetLastError();
 }
 
@@ -325,9 +331,9 @@ static hipError_t bwd_impl(const void* plan, int32_t n, int32_t W, int32_t H, fl
                            void* dk, void* dv, hipStream_t stream) {
   const PlanLayout lay = plan_layout(n, W);
   const KernelArgs a = kernel_args(plan, lay, n, W, H, eps);
-  const void* kern = reinterpret_cast<const void*>(&k_sla_bwd<T, D, PHI>);
-  hipLaunchKernelGGL((k_sla_bwd<T, D, PHI>), dim3(grid_size(kern, lay, n, H)), dim3(64 * kWaves), 0,
-                     stream, a, static_cast<const T*>(q), static_cast<const T*>(k),
+  const int grid = grid_size(reinterpret_cast<const void*>(&k_sla_bwd<T, D, PHI, false>), lay, n, H);
+  const auto kern = parts_fit(grid, n, H, kPartFill) ? &k_sla_bwd<T, D, PHI, true> : &k_sla_bwd<T, D, PHI, false>;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a, static_cast<const T*>(q), static_cast<const T*>(k),
                      static_cast<const T*>(v), static_cast<const T*>(dout), static_cast<T*>(dq),
                      static_cast<T*>(dk), static_cast<T*>(dv));
   return hipGetLastError();

@@ -449,7 +449,7 @@ __device__ __forceinline__ void stage_put(float* mat, int s, int i, int g, const
 // M += X^T Y over the rows [a, b) of a staged job (rows r0 .. r0 + 31).
 template <int D>
 __device__ __forceinline__ void stage_product(const float* X, const float* Y, int32_t r0, int32_t a, int32_t b,
-                                              int i, int g, State<D>& st) {
+                                              int i, int g, floatx4 (&M)[Geo<D>::NT][Geo<D>::NT]) {
   constexpr int NT = Geo<D>::NT;
 #pragma unroll
   for (int k = 0; k < kSliceRows / 4; ++k) {
@@ -464,7 +464,7 @@ __device__ __forceinline__ void stage_product(const float* X, const float* Y, in
     for (int et = 0; et < NT; ++et)
 #pragma unroll
       for (int ct = 0; ct < NT; ++ct)
-        st.M[et][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[et], y[ct], st.M[et][ct], 0, 0, 0);
+        M[et][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[et], y[ct], M[et][ct], 0, 0, 0);
   }
 }
 
@@ -510,7 +510,7 @@ __device__ __forceinline__ void state_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
       stage_put<D>(stage + kStageMat<D>, s, i, g, vv);
     }
     wave_lds_sync();
-    stage_product<D>(stage, stage + kStageMat<D>, r0, a, b, i, g, st);
+    stage_product<D>(stage, stage + kStageMat<D>, r0, a, b, i, g, st.M);
     wave_lds_sync();   // the tile may be written again
     return;
   } else {
@@ -845,7 +845,7 @@ __device__ __forceinline__ void qgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
   }
   if constexpr (!Ty<T>::kNarrow) {
     wave_lds_sync();
-    stage_product<D>(stage, stage + kStageMat<D>, r0, a, b, i, g, gs);
+    stage_product<D>(stage, stage + kStageMat<D>, r0, a, b, i, g, gs.M);
     wave_lds_sync();   // the tile may be written again
     return;
   } else {
@@ -920,6 +920,12 @@ __device__ __forceinline__ void kgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
 //                where the L2 serves the other heads' halves of each row.
 //   chunk items  one per chunk and group of up to 4 heads (one wave per head;
 //                with fewer than 4 heads, several chunks share a workgroup).
+//                A scene whose items do not fill the grid splits every chunk into
+//                2^part_bits items, each of which takes a share of its non-empty
+//                windows and reads their rows only: a chunk of thin windows is a
+//                serial chain of up to 32 of them on one wave while the rest of the
+//                chip idles.  fp16 forward + backward (with the build), 1,521
+//                windows: 2k rows 110 -> 42 us, 6k rows 76 -> 56 us.
 // Long items come first: they are the longest-running ones.
 //
 // Each wave software-pipelines its items: while item k computes, the plan entry
@@ -929,8 +935,12 @@ __device__ __forceinline__ void kgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
 struct Items {
   int32_t nL4, nL2, nC, H, hp, hw, cpw, hg;
   int32_t itemsL4, itemsL, total;
+  int32_t part_bits;
 };
+constexpr int kMaxPartBits = 4;
 
+// FILL: how many times the grid (in percent) the parts may fill; 0: no parts.
+template <int FILL, int BITS = kMaxPartBits>
 __device__ __forceinline__ Items work_items(const KernelArgs& a, const PlanHeader* hdr) {
   Items it;
   const int32_t nL = max(0, min(hdr->n_long, a.max_long));
@@ -944,7 +954,12 @@ __device__ __forceinline__ Items work_items(const KernelArgs& a, const PlanHeade
   it.hg = (a.H + 3) / 4;
   it.itemsL4 = ((it.nL4 + 7) & ~7) * a.H;
   it.itemsL = it.itemsL4 + ((it.nL2 + 7) & ~7) * it.hp;
-  it.total = it.itemsL + (it.nC + it.cpw - 1) / it.cpw * it.hg;
+  const int32_t chunks = (it.nC + it.cpw - 1) / it.cpw * it.hg;
+  it.part_bits = 0;
+  while (FILL > 0 && it.part_bits < BITS && (it.nC << (it.part_bits + 1)) <= a.W &&
+         (int64_t)chunks << (it.part_bits + 1) <= FILL * (int64_t)gridDim.x / 100)
+    ++it.part_bits;
+  it.total = it.itemsL + (chunks << it.part_bits);
   return it;
 }
 
@@ -954,6 +969,7 @@ struct WaveWork {
   int32_t ra, rb;  // rows (sorted positions)
   int32_t wb, we;  // windows
   int pair;        // long window: 0 = the four waves share it, 1 = waves 2m, 2m + 1 do
+  int part;        // chunk: which share of its windows
 };
 
 // Where item `item` puts wave wv (wave-uniform): table entry index (-1: none),
@@ -965,7 +981,7 @@ struct WaveWork {
 //     take the halves of head 2 x (item's pair) + m.
 struct Slot {
   int32_t idx;
-  int table, h, parts, piece;
+  int table, h, parts, piece, part;
 };
 
 __device__ __forceinline__ Slot item_slot(const Items& it, int32_t item, int wv) {
@@ -975,6 +991,7 @@ __device__ __forceinline__ Slot item_slot(const Items& it, int32_t item, int wv)
   sl.h = 0;
   sl.parts = 4;
   sl.piece = wv;
+  sl.part = 0;
   if (item >= it.total) return sl;
   if (item < it.itemsL4) {
     const int32_t r = item >> 3;
@@ -990,7 +1007,8 @@ __device__ __forceinline__ Slot item_slot(const Items& it, int32_t item, int wv)
     sl.h = h < it.H ? h : 0;
     if (j < it.nL2) sl.idx = it.nL4 + j;
   } else {
-    const int32_t b = item - it.itemsL;
+    const int32_t bp = item - it.itemsL, b = bp >> it.part_bits;
+    sl.part = bp - (b << it.part_bits);
     const int32_t grp = b / it.hg;
     const int sub = wv / it.hw;
     const int32_t c = grp * it.cpw + sub;
@@ -1015,6 +1033,7 @@ __device__ __forceinline__ WaveWork decode_work(const KernelArgs& a, const Slot&
   ww.h = sl.h;
   ww.ra = ww.rb = ww.wb = ww.we = 0;
   ww.pair = 0;
+  ww.part = sl.part;
   if (sl.idx < 0) return ww;
   if (sl.table == 0) {  // LongWin: window, row_begin, row_end
     const int32_t rs = max(0, min(e.y, a.n));
@@ -1053,8 +1072,9 @@ struct Stream {
   int32_t rb, re, wend;
   int32_t wp;      // first window of the loaded page
   int32_t a, b;    // rows of window wp + lane, clipped to [rb, re)
-  uint64_t live;   // lanes whose window is non-empty
+  uint64_t live;   // lanes whose window is non-empty (and of this item's part)
   int lane;
+  int part, bits;  // the share of every page's non-empty windows: part of 2^bits
   __device__ __forceinline__ void request(int32_t w0) {
     wp = w0;
     const int32_t w = wp + lane;
@@ -1064,7 +1084,28 @@ struct Stream {
       b = min(offs[w + 1], re);
     }
   }
-  __device__ __forceinline__ void settle() { live = __ballot(a < b); }
+  __device__ __forceinline__ void settle() {
+    live = __ballot(a < b);
+    if (bits != 0) {
+      const int rank = __popcll(live & ((1ull << lane) - 1)), cnt = __popcll(live);
+      live = __ballot(a < b && rank >= (cnt * part) >> bits && rank < (cnt * (part + 1)) >> bits);
+    }
+  }
+  // the rows of the first page's live windows, when it is the only page (rb, re
+  // otherwise)
+  __device__ __forceinline__ void rows(int32_t& begin, int32_t& end) {
+    begin = rb;
+    end = re;
+    if (bits == 0) return;
+    settle();
+    if (wp + 64 < wend) return;
+    if (live == 0) {
+      end = begin;
+      return;
+    }
+    begin = __builtin_amdgcn_readlane(a, __builtin_ctzll(live));
+    end = __builtin_amdgcn_readlane(b, 63 - __builtin_clzll(live));
+  }
   __device__ __forceinline__ bool next_window(WinCursor& j) {
     for (;;) {
       const int sh = j.w + 1 - wp;   // first lane after the current window
@@ -1115,12 +1156,12 @@ __device__ __forceinline__ void block_rows(BlockRows& br, int32_t base, int32_t 
 }
 
 // The matrices selected by `which` (bit m: mats[m]) of the block's rows into slot
-// order.  Sub-tiles past `end` are not read (and are zero); rows past `end`
-// inside a read sub-tile read row 0, which the math masks.
+// order.  Sub-tiles past `end` or before `begin` are not read (and are zero); rows
+// past `end` inside a read sub-tile read row 0, which the math masks.
 template <typename T, int D, int NM>
 __device__ __forceinline__ void block_fetch(Block<T, D, NM>& bk, const BlockRows& br, int32_t base,
                                             int32_t end, int32_t n, const T* const (&mats)[NM],
-                                            unsigned which, size_t rs, int col, int g) {
+                                            unsigned which, size_t rs, int col, int g, int32_t begin = INT32_MIN) {
   using F = Frag<T, Geo<D>::KS>;
 #pragma unroll
   for (int jj = 0; jj < kBlockJobs; ++jj)
@@ -1129,7 +1170,8 @@ __device__ __forceinline__ void block_fetch(Block<T, D, NM>& bk, const BlockRows
       const bool ok = (uint32_t)br.o[jj][s] < (uint32_t)n;
       bk.j[jj].ok[s] = ok;
       bk.j[jj].o[s] = ok ? br.o[jj][s] : 0;
-      const bool live = base + kSliceRows * jj + 16 * s < end;
+      const int32_t s0 = base + kSliceRows * jj + 16 * s;
+      const bool live = s0 < end && (begin == INT32_MIN || s0 + 16 > begin);
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         if (!(which & (1u << m))) continue;
@@ -1165,6 +1207,7 @@ __device__ __forceinline__ void pending_request(Pending& p, const KernelArgs& a,
                                                 int4 e, int wv, const int32_t* perm, int lane) {
   p.ww = decode_work(a, sl, e, wv);
   p.str.lane = lane;
+  p.str.part = p.str.bits = 0;
   p.str.offs = a.offs;
   p.str.rb = p.ww.ra;
   p.str.re = p.ww.rb;
@@ -1241,9 +1284,11 @@ __device__ __forceinline__ void block_rows_lds(BlockRows& br, const WaveWork& w,
 
 // The window stream of a chunk from its offsets slot (page 0; later pages are
 // read from the plan as they are reached).
-__device__ __forceinline__ void stream_lds(Stream& str, const WaveWork& w, const KernelArgs& a, const int32_t* slot,
-                                           int lane) {
+__device__ __forceinline__ void stream_lds(Stream& str, const WaveWork& w, const KernelArgs& a, const Items& it,
+                                           const int32_t* slot, int lane) {
   str.lane = lane;
+  str.part = w.part;
+  str.bits = w.kind == 1 ? it.part_bits : 0;
   str.offs = a.offs;
   str.rb = w.ra;
   str.re = w.rb;
@@ -1321,13 +1366,15 @@ struct WinIter {
     shared = ww.kind == 2;
     wc.w = ww.wb - 1;
     if (ww.kind == 1) {
-      str.settle();
+      if (str.bits == 0) str.settle();   // else settled by rows()
       return str.next_window(wc);
     }
     wc.ws = ww.ra;
     wc.we = ww.rb;
     return ww.kind == 2;
   }
+  // the window at hand
+  __device__ __forceinline__ int32_t window(const WaveWork& ww) const { return shared ? ww.wb : wc.w; }
   __device__ __forceinline__ bool next(const WaveWork& ww, Stream& str) {
     return ww.kind == 1 && str.next_window(wc);
   }
@@ -1343,7 +1390,7 @@ inline int resident_workgroups(const void* kernel) {
     const void* kernel;
     int dev, cap;
   };
-  static Entry cache[64] = {};
+  static Entry cache[128] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;
   for (const Entry& e : cache)
@@ -1369,7 +1416,7 @@ inline int resident_workgroups(const void* kernel) {
 // frame) get one persistent round whose waves prefetch item to item; large ones
 // (200k+ rows, several heads) get several rounds, so that the hardware
 // dispatcher balances items of very different cost.  At most enough workgroups
-// for every item the plan can hold; a multiple of 8.
+// for every item the plan can hold (chunks split into their parts); a multiple of 8.
 constexpr int64_t kRowHeadsPerWorkgroup = 300;
 
 inline int grid_size(const void* kernel, const PlanLayout& lay, int32_t n, int32_t H) {
@@ -1380,9 +1427,17 @@ inline int grid_size(const void* kernel, const PlanLayout& lay, int32_t n, int32
   int64_t k = ((int64_t)n * H + c * kRowHeadsPerWorkgroup / 2) / (c * kRowHeadsPerWorkgroup);
   if (k < 1) k = 1;
   int64_t g = k * c;
-  if (g > itemsL + itemsC) g = itemsL + itemsC;
+  if (g > itemsL + (itemsC << kMaxPartBits)) g = itemsL + (itemsC << kMaxPartBits);
   g = (g + 7) & ~7;
   return (int)(g < 8 ? 8 : g);
+}
+
+// Whether a launch of `grid` workgroups may find its chunks too few for it (a chunk
+// holds fewer than kMaxChunkRows rows), so that parts are worth their code: the
+// kernels without them, one to two percent faster on larger scenes, run otherwise.
+inline bool parts_fit(int grid, int32_t n, int32_t H, int fill) {
+  const int hw = H < 4 ? H : 4, cpw = 4 / hw, hg = (H + 3) / 4;
+  return (int64_t)n * hg * 2 * 100 <= (int64_t)grid * fill * kMaxChunkRows * cpw;
 }
 
 inline KernelArgs kernel_args(const void* plan, const PlanLayout& lay, int32_t n, int32_t W,
