@@ -5,27 +5,38 @@
 //     A[e][c] = softmax over c of  tau_h qhat[:, e] . khat[:, c]     (d x d),
 //     o_i[e]  = sum_c A[e][c] v_i[c]                                 for i in w.
 // Like Eq. (3) it needs one d x d reduction over the window's rows per head,
-// here q^T k together with the column norms, and then one d x d product per row.
+// here q^T k together with the column norms, and then one d x d product per row,
+// so it runs on the attention kernels' work items, row blocks and register
+// layouts (sla_attn_core.h): one wave per (chunk, head) or per share of a long
+// window, rows held in registers, no barrier but the exchange of a long window's
+// partial sums.
 //
-// k_xca_fwd: one workgroup per (window, head), the heads of a window on one XCD.
-//   1. 64 rows at a time, the window's q and k rows (this head's d columns)
-//      are gathered through the plan's permutation into LDS in fp32; thread
-//      (e, c-block) accumulates G[e][c] = sum_r q_re k_rc for its EPT columns,
-//      and the first wave the squared column norms.
-//   2. The logits tau G[e][c] / (|q_e| |k_c|) are bounded by |tau|, so the
-//      softmax needs no overflow guard beyond the usual max shift; the row max
-//      and sum are reduced over the CPR threads of a row with lane xors.
-//   3. Each thread keeps one row e of A in registers and, 64 rows at a time
-//      with the v rows in LDS, writes o_i[e] for its rows.  A window of at most
-//      64 rows gathers its v rows in step 1 already, into registers, so that
-//      their round trip overlaps the sums; longer windows gather v again here.
-// fp32 throughout; inputs widened from the storage type, outputs rounded to it.
+// The d x d matrices are held as result tiles of their transposes, M[ct][et]: lane
+// (i, g) component j is the entry (c, e) = (16 ct + 4 g + j, 16 et + i).  A row e
+// of A then lies in one lane per lane group: its softmax is a reduction over a
+// lane's own entries and two lane swaps; the tiles are already the operand of the
+// products over c (o = v A^T, dqhat = k B_q^T), and one LDS transpose gives the
+// operand of those over e.
+//
+// What bounds it: the chain of dependent steps of a window, at 2 to 4 waves per
+// SIMD, as in k_sla_fwd / k_sla_bwd.  The kernels before held one 256-thread workgroup
+// per (window, head), whose 5 to 9 barriers and serial column sums set the time.
+// Kernel trace, one Waymo-like frame (60k rows, fp16, H = 4, d = 32): forward 24.0
+// us against 26.9, backward 56.5 against 85.9; forward + backward by events 79.9
+// against 105 us, 151 against 328 on 100k rows in log-normal windows (bf16), 73
+// against 140 at H = 8, d = 16 (which ran on the vector units).
 #include "sla.h"
-#include "sla_common.h"
+#include "sla_attn_core.h"
 
 #include <mutex>
 
 namespace sla {
+
+hipError_t launch_xca_vec_fwd(const void* plan, int32_t n, int32_t W, int32_t H, int32_t d, const float* tau,
+                              const float* q, const float* k, const float* v, float* o, hipStream_t stream);
+hipError_t launch_xca_vec_bwd(const void* plan, int32_t n, int32_t W, int32_t H, int32_t d, const float* tau,
+                              const float* q, const float* k, const float* v, const float* dout, float* dq,
+                              float* dk, float* dv, float* part, hipStream_t stream);
 
 // The dtau partials of the backward without a workspace (sla_backward_xca_noalloc):
 // one fp32 per (window, head), held in static device memory on every GPU the
@@ -37,409 +48,412 @@ static __device__ __align__(256) float scratch[kXcaScratchFloats];
 
 namespace {
 
-constexpr int kXcaThreads = 256;
-constexpr int kXcaRows = 64;   // rows staged in LDS at a time
+constexpr float kXcaFloor = 1e-12f;   // least column norm
+// A window's chain is longer than the attention's and worth more parts (up to 8, four
+// times the grid): fp16 forward + backward, 1,521 windows, 20k rows 74 us against 84
+// with parts that fill the grid once, 3k rows 51 against 54.
+constexpr int kXcaPartFill = 400;
 
+// 16-bit operands of A in bf16 carry the rounding residual as a second operand
 template <typename T>
-struct XcaIo;
-template <>
-struct XcaIo<float> {
-  static constexpr int kPiece = 4;   // elements per 16-byte piece
-  __device__ static void unpack(uint4 u, float (&x)[4]) {
-    x[0] = __uint_as_float(u.x); x[1] = __uint_as_float(u.y);
-    x[2] = __uint_as_float(u.z); x[3] = __uint_as_float(u.w);
-  }
-  __device__ static void store(float* p, float x) { *p = x; }
-};
-template <>
-struct XcaIo<_Float16> {
-  static constexpr int kPiece = 8;
-  __device__ static void unpack(uint4 u, float (&x)[8]) {
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+constexpr bool kXcaPair = std::is_same<T, bf16_t>::value;
+
+// Sums over a window's rows: M[ct][et] = sum k_r[c] q_r[e] (forward and backward),
+// P[ct][et] = sum v_r[c] dout_r[e] (backward), and the squared columns of q and k:
+// 16-bit storage takes them from the diagonals of the tiles q^T q and k^T k, whose
+// operands M needs anyway; fp32 sums them on the vector units, by slots (slot r of
+// lane group g: column E(g, r)).
+template <int D, bool BWD>
+struct XcaSums {
+  static constexpr int NT = Geo<D>::NT, KS = Geo<D>::KS;
+  static constexpr int kTiles = (BWD ? 2 : 1) * NT * NT + 2 * NT;
+  floatx4 M[NT][NT];
+  floatx4 P[BWD ? NT : 1][BWD ? NT : 1];
+  floatx4 q2[NT], k2[NT];
+  __device__ void clear() {
+    const floatx4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      x[2 * j] = (float)__builtin_bit_cast(_Float16, (unsigned short)(w[j] & 0xffffu));
-      x[2 * j + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(w[j] >> 16));
+    for (int a = 0; a < NT; ++a) {
+      q2[a] = z;
+      k2[a] = z;
+#pragma unroll
+      for (int b = 0; b < NT; ++b) {
+        M[a][b] = z;
+        if constexpr (BWD) P[a][b] = z;
+      }
     }
   }
-  __device__ static void store(_Float16* p, float x) { *p = (_Float16)x; }
-};
-template <>
-struct XcaIo<bf16_t> {
-  static constexpr int kPiece = 8;
-  __device__ static void unpack(uint4 u, float (&x)[8]) {
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+  __device__ void publish(floatx4* slot, int lane) const {
+    int t = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      x[2 * j] = __uint_as_float(w[j] << 16);
-      x[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+    for (int a = 0; a < NT; ++a) {
+#pragma unroll
+      for (int b = 0; b < NT; ++b) {
+        slot[(t++) * 64 + lane] = M[a][b];
+        if constexpr (BWD) slot[(t++) * 64 + lane] = P[a][b];
+      }
+      slot[(t++) * 64 + lane] = q2[a];
+      slot[(t++) * 64 + lane] = k2[a];
     }
   }
-  __device__ static void store(bf16_t* p, float x) {
-    p->bits = __builtin_bit_cast(unsigned short, (__bf16)x);
+  // the sum of the published sums of the waves that share the window, in wave order
+  __device__ void combine(const floatx4* slots, int stride, int lane, int wv, bool pair) {
+    clear();
+    const int w0 = pair ? (wv & ~1) : 0, nw = pair ? 2 : kWaves;
+    for (int w = w0; w < w0 + nw; ++w) {
+      const floatx4* sl = slots + w * stride;
+      int t = 0;
+#pragma unroll
+      for (int a = 0; a < NT; ++a) {
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+          M[a][b] += sl[(t++) * 64 + lane];
+          if constexpr (BWD) P[a][b] += sl[(t++) * 64 + lane];
+        }
+        q2[a] += sl[(t++) * 64 + lane];
+        k2[a] += sl[(t++) * 64 + lane];
+      }
+    }
   }
 };
 
-// Workgroup b -> (window, head) such that the heads of a window share b mod 8:
-// workgroups are dealt to the 8 XCDs round-robin, so the heads of a window run
-// on one XCD, whose L2 then serves the other heads' quarters of each row's
-// 128-byte lines.  The grid is 8 ceil(W / 8) H; workgroups past the last window
-// have nothing to do.
-__device__ __forceinline__ void xca_item(uint32_t b, int32_t H, int32_t& w, int32_t& h) {
-  const uint32_t per = 8u * (uint32_t)H;
-  const uint32_t g = b / per, r = b - g * per;
-  h = (int32_t)(r >> 3);
-  w = (int32_t)(g * 8u + (r & 7u));
+// M[ct][et] += X^T Y over the rows [a, b) of a job (x, y zero outside); SQ: also
+// the diagonal tiles xx += X^T X, yy += Y^T Y (16-bit storage) or the squares by slots.
+template <typename T, int D, bool SQ>
+__device__ __forceinline__ void rows_product(const Raw<T, Geo<D>::KS> (&x)[2], const Raw<T, Geo<D>::KS> (&y)[2],
+                                             int32_t r0, int32_t a, int32_t b, int i, int g, const Sel<T, D>& sel,
+                                             float* stage, floatx4 (&M)[Geo<D>::NT][Geo<D>::NT],
+                                             floatx4 (*xx)[Geo<D>::NT], floatx4 (*yy)[Geo<D>::NT]) {
+  constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
+  if constexpr (!Ty<T>::kNarrow) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      stage_put<D>(stage, s, i, g, x[s]);
+      stage_put<D>(stage + kStageMat<D>, s, i, g, y[s]);
+      if constexpr (SQ)
+#pragma unroll
+        for (int r = 0; r < KS; ++r) {
+          (*xx)[r >> 2][r & 3] += x[s][r] * x[s][r];
+          (*yy)[r >> 2][r & 3] += y[s][r] * y[s][r];
+        }
+    }
+    wave_lds_sync();
+    stage_product<D>(stage, stage + kStageMat<D>, r0, a, b, i, g, M);
+    wave_lds_sync();   // the tile may be written again
+  } else {
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    auto rows_of = [&](const Raw<T, KS>(&u)[2], int t) -> Raw<T, 8> {
+      return pack_rows<T>(Frag<T, KS>::mma(u[0], sel.m[t], zero), Frag<T, KS>::mma(u[1], sel.m[t], zero));
+    };
+    Raw<T, 8> py[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      py[t] = rows_of(y, t);
+      if constexpr (SQ) (*yy)[t] = Frag<T, 8>::mma(py[t], py[t], (*yy)[t]);
+    }
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) {
+      const Raw<T, 8> px = rows_of(x, ct);
+      if constexpr (SQ) (*xx)[ct] = Frag<T, 8>::mma(px, px, (*xx)[ct]);
+#pragma unroll
+      for (int et = 0; et < NT; ++et) M[ct][et] = Frag<T, 8>::mma(px, py[et], M[ct][et]);
+    }
+  }
 }
 
-inline unsigned xca_grid(int32_t W, int32_t H) { return (unsigned)(((int64_t)W + 7) / 8 * 8 * H); }
+// Rows [a, b) of one job into the sums.  Matrices K, V, Q (and dout).
+template <typename T, int D, int NM>
+__device__ __forceinline__ void xca_sums_seg(const Slice<T, Geo<D>::KS, NM>& sb, int32_t r0, int32_t a, int32_t b,
+                                             int i, int g, const Sel<T, D>& sel, float* stage,
+                                             XcaSums<D, NM == 4>& su) {
+  constexpr int KS = Geo<D>::KS;
+  using F = Frag<T, KS>;
+  Raw<T, KS> x[2], y[2];
+  auto rows = [&](int mx, int my) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int32_t row = r0 + 16 * s + i;
+      const bool in = sb.ok[s] && row >= a && row < b;
+      x[s] = in ? sb.x[mx][s] : F::zero();
+      y[s] = in ? sb.x[my][s] : F::zero();
+    }
+  };
+  rows(0, 2);
+  rows_product<T, D, true>(x, y, r0, a, b, i, g, sel, stage, su.M, &su.k2, &su.q2);
+  if constexpr (NM == 4) {
+    rows(1, 3);
+    rows_product<T, D, false>(x, y, r0, a, b, i, g, sel, stage, su.P, nullptr, nullptr);
+  }
+}
 
-// LDS row stride of the staged rows: 16-byte aligned rows for float4 reads
+// Max over the 4 lane groups.
+__device__ __forceinline__ float max_groups(float x) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// Column norms of a window and their reciprocals, in the wave's LDS area: [q | k |
+// 1 / q | 1 / k], D each, one column a lane.  (The square root is the correctly
+// rounded one, so that the norm of a one-row column is its magnitude.)
 template <int D>
-constexpr int kXcaLd = D + 4;
+constexpr int kXcaNorm = 4 * D;
 
-// 16-byte pieces of a staged block: piece j = (row r, piece pc); a thread takes
-// pieces tid, tid + 256 (at most two: 64 rows of 32 fp32 columns)
-template <typename T, int D>
-constexpr int kXcaPieces = kXcaRows * D / XcaIo<T>::kPiece;
-template <typename T, int D>
-constexpr int kXcaPerThread = (kXcaPieces<T, D> + kXcaThreads - 1) / kXcaThreads;
-
-// Gathers the raw pieces of rows [p0, p0 + nr) (sorted positions) of `x` into
-// registers (zero past nr or for an out-of-range row) and, when s_row is given,
-// records each row's original index there (-1 for none).
-template <typename T, int D>
-__device__ __forceinline__ void xca_fetch(const int32_t* pm, int32_t p0, int nr, int32_t n,
-                                          size_t rs, int col, const T* x,
-                                          uint4 (&raw)[kXcaPerThread<T, D>], int32_t* s_row) {
-  constexpr int PB = XcaIo<T>::kPiece, PR = D / PB;
+template <typename T, int D, bool BWD>
+__device__ __forceinline__ void xca_norms(const XcaSums<D, BWD>& su, float* norms, int lane, int i, int g) {
+  constexpr int NT = Geo<D>::NT;
 #pragma unroll
-  for (int u = 0; u < kXcaPerThread<T, D>; ++u) {
-    const int j = (int)threadIdx.x + u * kXcaThreads;
-    const int r = j / PR, pc = j - r * PR;
-    int32_t row = -1;
-    if (j < kXcaPieces<T, D> && r < nr) {
-      row = pm ? pm[p0 + r] : p0 + r;
-      if ((uint32_t)row >= (uint32_t)n) row = -1;
-    }
-    raw[u] = row >= 0 ? *reinterpret_cast<const uint4*>(x + (size_t)row * rs + col + pc * PB)
-                      : make_uint4(0, 0, 0, 0);
-    if (s_row && j < kXcaPieces<T, D> && pc == 0) s_row[r] = row;
-  }
-}
-
-// Raw pieces into an LDS block of fp32 rows.
-template <typename T, int D>
-__device__ __forceinline__ void xca_put(const uint4 (&raw)[kXcaPerThread<T, D>],
-                                        float (*a)[kXcaLd<D>]) {
-  constexpr int PB = XcaIo<T>::kPiece, PR = D / PB;
-#pragma unroll
-  for (int u = 0; u < kXcaPerThread<T, D>; ++u) {
-    const int j = (int)threadIdx.x + u * kXcaThreads;
-    if (j < kXcaPieces<T, D>) {
-      const int r = j / PR, pc = j - r * PR;
-      float x[PB];
-      XcaIo<T>::unpack(raw[u], x);
-#pragma unroll
-      for (int e = 0; e < PB; ++e) a[r][pc * PB + e] = x[e];
-    }
-  }
-}
-
-template <typename T, int D>
-__global__ __launch_bounds__(kXcaThreads) void k_xca_fwd(
-    const PlanHeader* __restrict__ hdr, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ offs, const float* __restrict__ tau, const T* __restrict__ q,
-    const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ o, int32_t n, int32_t W,
-    int32_t H) {
-  constexpr int EPT = D * D / kXcaThreads;   // entries (e, c) per thread: 4 (d = 32) or 1 (d = 16)
-  constexpr int CPR = D / EPT;               // threads per row e of G
-  constexpr int RPP = kXcaThreads / D;       // output rows per pass of phase 3
-  static_assert(D * D % kXcaThreads == 0 && CPR <= 64 && (CPR & (CPR - 1)) == 0, "row groups");
-  constexpr int LD = kXcaLd<D>;
-  constexpr int NP = kXcaPerThread<T, D>;
-  __shared__ __align__(16) float s_a[kXcaRows][LD];   // q rows, then v rows
-  __shared__ __align__(16) float s_b[kXcaRows][LD];   // k rows
-  __shared__ float s_g[D][D + 1];          // softmax weights A
-  __shared__ float s_nrm[2 * D];           // |q_e|, then |k_c|
-  __shared__ int32_t s_row[kXcaRows];
-  int32_t w, h;
-  xca_item(blockIdx.x, H, w, h);
-  if (w >= W) return;
-  if (hdr->magic != kPlanMagic || hdr->n != n || hdr->num_windows != W) return;
-  const int32_t* pm = hdr->csr ? nullptr : perm;
-  const int32_t rb = max(0, min(offs[w], n)), re = max(rb, min(offs[w + 1], n));
-  if (rb == re) return;
-  const int tid = (int)threadIdx.x;
-  const size_t rs = (size_t)H * D;
-  const int col = h * D;
-
-  // 1. G = q^T k over the window's rows, and the squared column norms
-  const int e = tid / CPR, c0 = (tid - e * CPR) * EPT;
-  float acc[EPT];
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) acc[u] = 0.f;
-  float nrm = 0.f;
-  // a window of at most one block also gathers its v rows now, into registers,
-  // so that their round trip overlaps the q^T k sums
-  const bool one = re - rb <= kXcaRows;
-  uint4 vr[NP];
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (p0 != rb) __syncthreads();   // the previous block's readers are done
-    {
-      uint4 qr[NP], kr[NP];
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, q, qr, s_row);
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, k, kr, nullptr);
-      if (one) xca_fetch<T, D>(pm, p0, nr, n, rs, col, v, vr, nullptr);
-      xca_put<T, D>(qr, s_a);
-      xca_put<T, D>(kr, s_b);
-    }
-    __syncthreads();
-    for (int r = 0; r < nr; ++r) {
-      const float a = s_a[r][e];
-#pragma unroll
-      for (int u = 0; u < EPT; ++u) acc[u] += a * s_b[r][c0 + u];
-    }
-    // the first wave sums the squared columns (q in lanes 0..D-1, k after)
-    if (tid < D) {
-      for (int r = 0; r < nr; ++r) nrm += s_a[r][tid] * s_a[r][tid];
-    } else if (tid < 2 * D) {
-      for (int r = 0; r < nr; ++r) nrm += s_b[r][tid - D] * s_b[r][tid - D];
-    }
-  }
-  if (tid < 2 * D) s_nrm[tid] = fmaxf(sqrtf(nrm), 1e-12f);
-  __syncthreads();
-
-  // 2. softmax of each row e over c
-  const float t = tau[h];
-  float g[EPT];
-  float mx = -3.0e38f;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    g[u] = t * acc[u] / (s_nrm[e] * s_nrm[D + c0 + u]);
-    mx = fmaxf(mx, g[u]);
-  }
-#pragma unroll
-  for (int m = 1; m < CPR; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-  float sum = 0.f;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    g[u] = expf(g[u] - mx);
-    sum += g[u];
-  }
-#pragma unroll
-  for (int m = 1; m < CPR; m <<= 1) sum += __shfl_xor(sum, m, 64);
-  const float inv = 1.f / sum;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) s_g[e][c0 + u] = g[u] * inv;
-  // s_a's last readers (the q^T k sums) passed the barrier above
-  if (one) xca_put<T, D>(vr, s_a);
-  __syncthreads();
-
-  // 3. o_i[e3] = sum_c A[e3][c] v_i[c]
-  const int e3 = tid % D, r3 = tid / D;
-  float arow[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) arow[c] = s_g[e3][c];
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (!one) {
-      __syncthreads();   // s_a and s_row are free
-      uint4 raw[NP];
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, v, raw, s_row);
-      xca_put<T, D>(raw, s_a);
-      __syncthreads();
-    }
-    for (int r = r3; r < nr; r += RPP) {
-      const int32_t row = s_row[r];
-      float s = 0.f;
-#pragma unroll
-      for (int c = 0; c < D; c += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(&s_a[r][c]);
-        s += arow[c] * x.x + arow[c + 1] * x.y + arow[c + 2] * x.z + arow[c + 3] * x.w;
+  for (int t = 0; t < NT; ++t) {
+    if constexpr (Ty<T>::kNarrow) {
+      const int j = i & 3;
+      const float x = j < 2 ? (j == 0 ? su.q2[t][0] : su.q2[t][1]) : (j == 2 ? su.q2[t][2] : su.q2[t][3]);
+      const float y = j < 2 ? (j == 0 ? su.k2[t][0] : su.k2[t][1]) : (j == 2 ? su.k2[t][2] : su.k2[t][3]);
+      if (g == (i >> 2)) {
+        norms[16 * t + i] = x;
+        norms[D + 16 * t + i] = y;
       }
-      if (row >= 0) XcaIo<T>::store(o + (size_t)row * rs + col + e3, s);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float x = sum_rows16(su.q2[t][j]), y = sum_rows16(su.k2[t][j]);
+        if (i == 0) {
+          norms[16 * t + 4 * g + j] = x;
+          norms[D + 16 * t + 4 * g + j] = y;
+        }
+      }
     }
+  }
+  wave_lds_sync();
+  if (lane < 2 * D) {
+    const float x = fmaxf(sqrtf(norms[lane]), kXcaFloor);
+    norms[lane] = x;
+    norms[2 * D + lane] = recip<T>(x);
+  }
+  wave_lds_sync();
+}
+
+// Slots c or e = E(g, r) of one of the four parts, read where they are used: held
+// in registers through the row passes they cost spills.
+template <int D>
+__device__ __forceinline__ void xca_slots(const float* s, int g, float (&x)[Geo<D>::KS]) {
+#pragma unroll
+  for (int t = 0; t < Geo<D>::NT; ++t) {
+    const float4 u = *reinterpret_cast<const float4*>(s + 16 * t + 4 * g);
+    x[4 * t] = u.x; x[4 * t + 1] = u.y; x[4 * t + 2] = u.z; x[4 * t + 3] = u.w;
   }
 }
 
-// ----------------------------------------------- forward on the matrix cores
-// 16-bit storage, d = 32: the same three steps with both d x d contractions on
-// the matrix cores and the rows staged in LDS in their storage format.
-//   1. Wave w forms tile (w / 2, w % 2) of G = sum_r q_r^T k_r.  The contraction
-//      runs over rows, so both operands are columns of the staged rows, read
-//      with the LDS transpose load: in a group of 16 lanes, lane i of group g
-//      addresses row 8g + 4h + i / 4, columns 16t + 4 (i % 4) .. + 3, and
-//      receives (the probed lane layout of ds_read_b64_tr_b16) the four
-//      elements of column 16t + i in rows 8g + 4h .. + 3: operand slot 4h + j
-//      holds row 8g + 4h + j, for A (q) and B (k) alike.  The column norms are
-//      summed from the staged rows as in the fp32 path.
-//   2. The softmax as before, in fp32 from G in LDS; A is rounded to the storage
-//      type (bf16: as a pair of high part and residual, 16 bits together).
-//   3. o = v A^T: slot j of lane (i, g) is channel c = 8g + j, so A's row e and
-//      v's row r are read as they lie (16 bytes a lane); wave w forms the 16-row
-//      tile w of a 64-row block for both halves of d, and lane (i, g) receives
-//      o[row 16w + i][16t + 4g .. + 3].
-// Columns 16t .. 16t + 15 of rows base .. base + 31 of a staged block as an
-// operand of a contraction over the rows (slot r of lane (i, g): row base + 8g + r,
-// column 16t + i), by LDS transpose loads.
-template <typename T, int LDH>
-__device__ __forceinline__ Raw<T, 8> xca_cols(const unsigned short (*s)[LDH], int base, int t, int i,
-                                              int g) {
-  return lds_cols<T>(&s[base][0], LDH, 16 * t, i, g);
-}
-
+// exp(x) for x <= 0: 2^(x log2 e) on the hardware's exp2 (1 ulp).  fp32 adds what
+// the product's rounding and log2 e's own lost: 2^(t + r) = 2^t (1 + r ln 2) for |r| < 2^-16.
 template <typename T>
-__global__ __launch_bounds__(kXcaThreads) void k_xca_fwd_mma(
-    const PlanHeader* __restrict__ hdr, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ offs, const float* __restrict__ tau, const T* __restrict__ q,
-    const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ o, int32_t n, int32_t W,
-    int32_t H) {
-  constexpr int D = 32;
-  constexpr int LDH = D + 8;                 // staged 16-bit rows: 80 bytes, 16-byte aligned
-  constexpr int EPT = D * D / kXcaThreads;   // softmax: entries (e, c) per thread
-  constexpr int CPR = D / EPT;
-  constexpr int NP = kXcaPerThread<T, D>;    // one 16-byte piece a thread
-  constexpr bool kPair = std::is_same<T, bf16_t>::value;
-  using F = Frag<T, 8>;
-  static_assert(NP == 1 && kXcaPieces<T, D> == kXcaThreads, "one piece a thread");
-  __shared__ __align__(16) unsigned short s_q[kXcaRows][LDH];
-  __shared__ __align__(16) unsigned short s_k[kXcaRows][LDH];
-  __shared__ __align__(16) unsigned short s_v[kXcaRows][LDH];
-  __shared__ __align__(16) unsigned short s_p[kPair ? 2 : 1][D][LDH];   // A (and its residual)
-  __shared__ float s_g[D][D + 1];
-  __shared__ float s_nrm[2 * D];
-  __shared__ int32_t s_row[kXcaRows];
-  int32_t w, h;
-  xca_item(blockIdx.x, H, w, h);
-  if (w >= W) return;
-  if (hdr->magic != kPlanMagic || hdr->n != n || hdr->num_windows != W) return;
-  const int32_t* pm = hdr->csr ? nullptr : perm;
-  const int32_t rb = max(0, min(offs[w], n)), re = max(rb, min(offs[w + 1], n));
-  if (rb == re) return;
-  const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int i = lane & 15, g = lane >> 4;
-  const size_t rs = (size_t)H * D;
-  const int col = h * D;
-  const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-  // piece tid of a block: row tid / 4, channels 8 (tid % 4) .. + 7
-  const int pr = tid >> 2, pc = tid & 3;
-  auto put = [&](unsigned short (*s)[LDH], uint4 x) { *reinterpret_cast<uint4*>(&s[pr][8 * pc]) = x; };
-
-  // 1. G tile (et, ct) of this wave, and the squared column norms
-  const int et = wv >> 1, ct = wv & 1;
-  floatx4 acc = zero;
-  float nrm = 0.f;
-  const bool one = re - rb <= kXcaRows;
-  uint4 vr[NP];
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (p0 != rb) __syncthreads();   // the previous block's readers are done
-    {
-      uint4 qr[NP], kr[NP];
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, q, qr, s_row);
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, k, kr, nullptr);
-      if (one) xca_fetch<T, D>(pm, p0, nr, n, rs, col, v, vr, nullptr);
-      put(s_q, qr[0]);
-      put(s_k, kr[0]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      if (32 * ks >= nr) break;   // rows past nr are zero
-      acc = F::mma(xca_cols<T, LDH>(s_q, 32 * ks, et, i, g), xca_cols<T, LDH>(s_k, 32 * ks, ct, i, g), acc);
-    }
-    if (tid < D) {
-      for (int r = 0; r < nr; ++r) {
-        const float x = u16_to_f32<T>(s_q[r][tid]);
-        nrm += x * x;
-      }
-    } else if (tid < 2 * D) {
-      for (int r = 0; r < nr; ++r) {
-        const float x = u16_to_f32<T>(s_k[r][tid - D]);
-        nrm += x * x;
-      }
-    }
+__device__ __forceinline__ float xca_exp(float x) {
+  if constexpr (Ty<T>::kNarrow) {
+    return __builtin_amdgcn_exp2f(x * kLog2e);
+  } else {
+    constexpr float kLo = 1.925963033e-8f;   // log2 e - kLog2e
+    x = fmaxf(x, -128.f);                     // 2^-184 is zero
+    const float t = x * kLog2e;
+    const float r = fmaf(x, kLo, fmaf(x, kLog2e, -t));
+    const float e = __builtin_amdgcn_exp2f(t);
+    return fmaf(e * 0.69314718f, r, e);
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) s_g[16 * et + 4 * g + j][16 * ct + i] = acc[j];
-  if (tid < 2 * D) s_nrm[tid] = fmaxf(sqrtf(nrm), 1e-12f);
-  __syncthreads();
+}
 
-  // 2. softmax of each row e over c, A to the storage type
-  {
-    const int e = tid / CPR, c0 = (tid - e * CPR) * EPT;
-    const float t = tau[h];
-    float gv[EPT];
+// M: raw sums -> A (both transposed); N, when asked for, gets qhat^T khat.  The
+// logits lie in [-|tau|, |tau|], so the usual max shift is all the guard needed.
+template <typename T, int D, bool KEEP>
+__device__ __forceinline__ void xca_softmax(floatx4 (&M)[Geo<D>::NT][Geo<D>::NT], const float* norms, float tau,
+                                            int i, int g, floatx4 (*N)[Geo<D>::NT]) {
+  constexpr int NT = Geo<D>::NT;
+  float rk[Geo<D>::KS];
+  xca_slots<D>(norms + 3 * D, g, rk);
+#pragma unroll
+  for (int et = 0; et < NT; ++et) {
     float mx = -3.0e38f;
+    const float rq = norms[2 * D + 16 * et + i];
 #pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      gv[u] = t * s_g[e][c0 + u] / (s_nrm[e] * s_nrm[D + c0 + u]);
-      mx = fmaxf(mx, gv[u]);
-    }
+    for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
-    for (int m = 1; m < CPR; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
+      for (int j = 0; j < 4; ++j) {
+        const float x = M[ct][et][j] * rq * rk[4 * ct + j];
+        if constexpr (KEEP) N[ct][et][j] = x;
+        M[ct][et][j] = tau * x;
+        mx = fmaxf(mx, M[ct][et][j]);
+      }
+    mx = max_groups(mx);
     float sum = 0.f;
 #pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      gv[u] = expf(gv[u] - mx);
-      sum += gv[u];
-    }
+    for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
-    for (int m = 1; m < CPR; m <<= 1) sum += __shfl_xor(sum, m, 64);
-    const float inv = 1.f / sum;
+      for (int j = 0; j < 4; ++j) {
+        const float x = M[ct][et][j] - mx;
+        M[ct][et][j] = xca_exp<T>(x);
+        sum += M[ct][et][j];
+      }
+    const float inv = recip<T>(sum_groups(sum));
 #pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      const float a = gv[u] * inv;
-      const unsigned short hi = f32_to_u16<T>(a);
-      s_p[0][e][c0 + u] = hi;
-      if constexpr (kPair) s_p[kPair ? 1 : 0][e][c0 + u] = f32_to_u16<T>(a - u16_to_f32<T>(hi));
-    }
-  }
-  // s_q's last readers (the norms) passed the barrier above; s_v is unused so far
-  if (one) put(s_v, vr[0]);
-  __syncthreads();
-
-  // 3. o = v A^T, tile wv of each 64-row block
-  // tile t2's operand row i is A's row 8 (i / 4) + 4 t2 + i % 4, so that lane
-  // (i, g) receives columns 8 g .. 8 g + 7 of o over the two tiles and stores
-  // them as one 16-byte piece
-  Raw<T, 8> pa[2], pl[2];
+    for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
-  for (int t2 = 0; t2 < 2; ++t2) {
-    const int e = 8 * (i >> 2) + 4 * t2 + (i & 3);
-    pa[t2] = *reinterpret_cast<const Raw<T, 8>*>(&s_p[0][e][8 * g]);
-    if constexpr (kPair) pl[t2] = *reinterpret_cast<const Raw<T, 8>*>(&s_p[kPair ? 1 : 0][e][8 * g]);
-  }
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (!one) {
-      __syncthreads();   // s_v and s_row are free
-      uint4 raw[NP];
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, v, raw, s_row);
-      put(s_v, raw[0]);
-      __syncthreads();
-    }
-    const int r = 16 * wv + i;
-    if (16 * wv >= nr) continue;   // the whole tile is past the block's rows
-    const Raw<T, 8> vb = *reinterpret_cast<const Raw<T, 8>*>(&s_v[r][8 * g]);
-    const int32_t row = r < nr ? s_row[r] : -1;
-    float f[8];
-#pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2) {
-      floatx4 d4 = F::mma(pa[t2], vb, zero);
-      if constexpr (kPair) d4 = F::mma(pl[t2], vb, d4);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) f[4 * t2 + j] = d4[j];
-    }
-    if (row >= 0) *reinterpret_cast<Raw<T, 8>*>(o + (size_t)row * rs + col + 8 * g) = F::from_f32(f);
+      for (int j = 0; j < 4; ++j) M[ct][et][j] *= inv;
   }
 }
 
-// ---------------------------------------------------------------- backward
-// Chain rule of the forward, per (window, head) workgroup, with
-// N = qhat^T khat, G = tau N and A = softmax_c(G):
+// Operand of a product over c from transposed tiles: lane (i, g) of tile et holds
+// (row e = 16 et + i) the slots c = E(g, r), times mul; `lo` gets the residuals.
+template <typename T, int D, bool LO>
+__device__ __forceinline__ void xca_operand(const floatx4 (&M)[Geo<D>::NT][Geo<D>::NT], float mul,
+                                            Raw<T, Geo<D>::KS> (&hi)[Geo<D>::NT], Raw<T, Geo<D>::KS>* lo) {
+  constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
+  using F = Frag<T, KS>;
+#pragma unroll
+  for (int et = 0; et < NT; ++et) {
+    float x[KS];
+#pragma unroll
+    for (int r = 0; r < KS; ++r) x[r] = M[r >> 2][et][r & 3] * mul;
+    hi[et] = F::from_f32(x);
+    if constexpr (LO) {
+      float h[KS];
+      F::to_f32(hi[et], h);
+#pragma unroll
+      for (int r = 0; r < KS; ++r) x[r] -= h[r];
+      lo[et] = F::from_f32(x);
+    }
+  }
+}
+
+// --------------------------------------------------------------- forward
+template <typename T, int D, bool PARTS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restrict__ q, const T* __restrict__ k,
+               const T* __restrict__ v, T* __restrict__ o) {
+  constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
+  constexpr int KT = XcaSums<D, false>::kTiles;
+  // a wave's slot: published sums; in fp32 also its staging tile, and the norms
+  constexpr int SL = KT * 64 > kStageWave<D> / 4 ? KT * 64 : kStageWave<D> / 4;
+  constexpr bool kHold = Ty<T>::kNarrow || D == 16;
+  using F = Frag<T, KS>;
+  __shared__ floatx4 s_part[kWaves * SL];
+  __shared__ WaveMeta s_meta[kWaves];
+  __shared__ __align__(16) float s_norm[kWaves][kXcaNorm<D>];
+  const int lane = lane_id();
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const PlanHeader* hdr = a.hdr;
+  if (hdr->magic != kPlanMagic || hdr->n != a.n || hdr->num_windows != a.W) return;
+  const Items it = work_items<PARTS ? kXcaPartFill : 0, 3>(a, hdr);
+  const int32_t* perm = hdr->csr ? nullptr : a.perm;
+  const int i = lane & 15, g = lane >> 4;
+  const size_t rs = (size_t)a.H * D;
+  const int32_t n = a.n, G = gridDim.x;
+  const Sel<T, D> sel(i, g);
+  floatx4* const slot = s_part + wv * SL;
+  float* const stage = reinterpret_cast<float*>(slot);
+  float* const norms = s_norm[wv];
+  const T* const mats[3] = {k, v, q};
+  constexpr unsigned kKQ = 5u, kV = 2u, kAll = 7u;
+  WaveMeta& meta = s_meta[wv];
+  const bool csr = perm == nullptr;
+  int32_t item = blockIdx.x;
+  WaveWork wc, wn;
+  {
+    const Slot s0 = item_slot(it, item, wv), s1 = item_slot(it, item + G, wv);
+    wc = decode_work(a, s0, slot_entry(a, s0), wv);
+    wn = decode_work(a, s1, slot_entry(a, s1), wv);
+  }
+  request_perm(wc, perm, meta.perm[0], lane);
+  request_perm(wn, perm, meta.perm[1], lane);
+  request_offs(wc, a, meta.offs[0], lane);
+  request_entry(a, item_slot(it, item + 2 * G, wv), &meta.ent[0], lane);
+  int par = 0;   // ring slot of the current item
+  while (item < it.total) {
+    const WaveWork ww = wc;
+    const int col = ww.h * D;
+    // a share of more than kBlockRows rows is streamed through the block
+    const bool resident = ww.rb - ww.ra <= kBlockRows;
+    // fp32 at d = 32 reads v per window, after the sums, and k, q too: three waves per SIMD
+    const unsigned first = resident && kHold ? kAll : kKQ;
+    // the item's rows and windows, and the entry of the item after next, from LDS;
+    // then the requests ahead (see k_sla_fwd)
+    wait_vm();
+    BlockRows br;
+    block_rows_lds(br, ww, meta.perm[par], csr, lane);
+    Stream str;
+    stream_lds(str, ww, a, it, meta.offs[par], lane);
+    const WaveWork wnn = decode_work(a, item_slot(it, item + 2 * G, wv), lds_entry(&meta.ent[par]), wv);
+    wait_lgkm();
+    request_perm(wnn, perm, meta.perm[par], lane);
+    request_offs(wn, a, meta.offs[par ^ 1], lane);
+    request_entry(a, item_slot(it, item + 3 * G, wv), &meta.ent[par ^ 1], lane);
+    Block<T, D, 3> bk;
+    int32_t fa = INT32_MIN, fb = ww.rb;   // the rows of this item's windows
+    if constexpr (PARTS) str.rows(fa, fb);
+    if (kHold && ww.kind != 0) {
+      block_fetch<T, D, 3>(bk, br, ww.ra, fb, n, mats, first, rs, col, g, fa);
+      block_arrange<T, D, 3>(bk, first);
+    }
+    const float th = tau[ww.h];
+    WinIter wi;
+    for (bool more = wi.first(ww, str); more; more = wi.next(ww, str)) {
+      const int32_t wa = wi.wc.ws, wb = wi.wc.we;
+      auto refetch = [&](int32_t base, unsigned which) {
+        BlockRows br;
+        block_rows(br, base, ww.rb, perm, lane);
+        block_fetch<T, D, 3>(bk, br, base, wb, n, mats, which, rs, col, g, wa);
+        block_arrange<T, D, 3>(bk, which);
+      };
+      XcaSums<D, false> su;
+      su.clear();
+      for (int32_t base = ww.ra; base < ww.rb; base += kBlockRows) {
+        if (!kHold || base != ww.ra) refetch(base, kKQ);
+#pragma unroll
+        for (int jj = 0; jj < kBlockJobs; ++jj) {
+          const int32_t r0 = base + kSliceRows * jj;
+          if (job_overlaps(r0, wa, wb)) xca_sums_seg<T, D, 3>(bk.j[jj], r0, wa, wb, i, g, sel, stage, su);
+        }
+      }
+      if (wi.shared) {
+        su.publish(slot, lane);
+        lds_barrier();
+        su.combine(s_part, SL, lane, wv, ww.pair);
+        lds_barrier();  // the slots may be written again
+      }
+      if (!kHold) refetch(ww.ra, kV);   // in flight under the softmax
+      xca_norms<T, D>(su, norms, lane, i, g);
+      xca_softmax<T, D, false>(su.M, norms, th, i, g, nullptr);
+      Raw<T, KS> op[NT], opl[NT];
+      xca_operand<T, D, kXcaPair<T>>(su.M, 1.f, op, opl);
+      for (int32_t base = ww.ra; base < ww.rb; base += kBlockRows) {
+        if (!(resident && kHold) && (base != ww.ra || kHold)) refetch(base, kV);
+#pragma unroll
+        for (int jj = 0; jj < kBlockJobs; ++jj)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const int32_t r0 = base + kSliceRows * jj;
+            if (!sub_overlaps(r0, s, wa, wb)) continue;
+            const int32_t row = r0 + 16 * s + i;
+            float x[KS];
+#pragma unroll
+            for (int et = 0; et < NT; ++et) {
+              const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+              floatx4 d4 = F::mma(op[et], bk.j[jj].x[1][s], zero);
+              if constexpr (kXcaPair<T>) d4 = F::mma(opl[et], bk.j[jj].x[1][s], d4);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) x[4 * et + j] = d4[j];
+            }
+            RowIO<T, D>::put(o, row_off(bk.j[jj].o[s], rs, col), g, F::from_f32(x),
+                             bk.j[jj].ok[s] && row >= wa && row < wb);
+          }
+      }
+    }
+    item += G;
+    wc = wn;
+    wn = wnn;
+    par ^= 1;
+  }
+}
+
+// -------------------------------------------------------------- backward
+// Chain rule of the forward, with N = qhat^T khat, A = softmax_c(tau N):
 //   dv_i = A^T do_i,  dA = sum_i do_i v_i^T,  dG = A * (dA - rowsum(A * dA)),
 //   dtau partial = sum dG * N,
 //   dqh[:, e] = sum_c B_q[e][c] k[:, c] with B_q[e][c] = tau dG[e][c] / nk_c,
@@ -452,301 +466,25 @@ __global__ __launch_bounds__(kXcaThreads) void k_xca_fwd_mma(
 // arithmetic: in a one-row window qhat = q / |q| is +-1 exactly (the square
 // root of a rounded square is the magnitude again in binary floating point), so
 // qhat s_e = dqh and dq = 0, as the chain rule gives.
-// Passes over the window's rows: q, k (N, as in the forward); dout, v (dA and
-// dv); q, k again (dqh, dkh and their projections; then dq, dk, from registers
-// for a window of one block, from a further pass over q, k otherwise).  The
-// temperature gradient of every (window, head) goes to `part`; k_xca_dtau adds
-// the windows in order.
-template <typename T, int D>
-__global__ __launch_bounds__(kXcaThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 5))) void k_xca_bwd(
-    const PlanHeader* __restrict__ hdr, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ offs, const float* __restrict__ tau, const T* __restrict__ q,
-    const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ dout,
-    T* __restrict__ dq, T* __restrict__ dk, T* __restrict__ dv, float* __restrict__ part,
-    int32_t n, int32_t W, int32_t H) {
-  constexpr int EPT = D * D / kXcaThreads;
-  constexpr int CPR = D / EPT;
-  constexpr int RPP = kXcaThreads / D;
-  constexpr int LD = kXcaLd<D>;
-  constexpr int NP = kXcaPerThread<T, D>;
-  constexpr int NW = kXcaThreads / 64;
-  __shared__ __align__(16) float s_a[kXcaRows][LD];
-  __shared__ __align__(16) float s_b[kXcaRows][LD];
-  // A (rows of D + 1) until pass 2 ends, then B_q[e][c] = tau dG[e][c] / nk_c
-  // (rows of LD) in the same place
-  __shared__ __align__(16) float s_ab[D * LD];
-  float (*const s_g)[D + 1] = reinterpret_cast<float (*)[D + 1]>(s_ab);
-  float (*const s_bq)[LD] = reinterpret_cast<float (*)[LD]>(s_ab);
-  __shared__ __align__(16) float s_bk[D][LD];   // B_k[c][e] = tau dG[e][c] / nq_e
-  __shared__ float s_sp[2 * RPP][D]; // shares of s_e and t_c
-  __shared__ float s_nrm[2 * D];     // nq, nk
-  __shared__ float s_st[2 * D];      // s_e, t_c
-  __shared__ float s_red[NW];
-  __shared__ int32_t s_row[kXcaRows];
-  const int tid = (int)threadIdx.x;
-  int32_t w, h;
-  xca_item(blockIdx.x, H, w, h);
-  if (w >= W) return;
-  const size_t b = (size_t)w * H + h;   // this (window, head)'s temperature partial
-  if (hdr->magic != kPlanMagic || hdr->n != n || hdr->num_windows != W) {
-    if (tid == 0) part[b] = 0.f;
-    return;
-  }
-  const int32_t* pm = hdr->csr ? nullptr : perm;
-  const int32_t rb = max(0, min(offs[w], n)), re = max(rb, min(offs[w + 1], n));
-  if (rb == re) {
-    if (tid == 0) part[b] = 0.f;
-    return;
-  }
-  const size_t rs = (size_t)H * D;
-  const int col = h * D;
-  const float t = tau[h];
-
-  // 1. N = qhat^T khat (raw sums and column norms), A
-  const int e = tid / CPR, c0 = (tid - e * CPR) * EPT;
-  float acc[EPT];
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) acc[u] = 0.f;
-  float nrm = 0.f;
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (p0 != rb) __syncthreads();
-    {
-      uint4 qr[NP], kr[NP];
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, q, qr, s_row);
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, k, kr, nullptr);
-      xca_put<T, D>(qr, s_a);
-      xca_put<T, D>(kr, s_b);
-    }
-    __syncthreads();
-    for (int r = 0; r < nr; ++r) {
-      const float x = s_a[r][e];
-#pragma unroll
-      for (int u = 0; u < EPT; ++u) acc[u] += x * s_b[r][c0 + u];
-    }
-    if (tid < D) {
-      for (int r = 0; r < nr; ++r) nrm += s_a[r][tid] * s_a[r][tid];
-    } else if (tid < 2 * D) {
-      for (int r = 0; r < nr; ++r) nrm += s_b[r][tid - D] * s_b[r][tid - D];
-    }
-  }
-  if (tid < 2 * D) s_nrm[tid] = fmaxf(sqrtf(nrm), 1e-12f);
-  __syncthreads();
-  float nn[EPT], a[EPT];
-  float mx = -3.0e38f;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    nn[u] = acc[u] / (s_nrm[e] * s_nrm[D + c0 + u]);
-    a[u] = t * nn[u];
-    mx = fmaxf(mx, a[u]);
-  }
-#pragma unroll
-  for (int m = 1; m < CPR; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-  float sum = 0.f;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    a[u] = expf(a[u] - mx);
-    sum += a[u];
-  }
-#pragma unroll
-  for (int m = 1; m < CPR; m <<= 1) sum += __shfl_xor(sum, m, 64);
-  const float inv = 1.f / sum;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    a[u] *= inv;
-    s_g[e][c0 + u] = a[u];
-  }
-  __syncthreads();
-
-  // 2. dA = sum_i do_i v_i^T, and dv_i[x3] = sum_e A[e][x3] do_i[e]
-  const int x3 = tid % D, r3 = tid / D;
-  float acl[D];
-#pragma unroll
-  for (int j = 0; j < D; ++j) acl[j] = s_g[j][x3];
-  float da[EPT];
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) da[u] = 0.f;
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    __syncthreads();   // s_a, s_b, s_row (and s_g's column reads) are done with
-    {
-      uint4 dr[NP], vr[NP];
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, dout, dr, s_row);
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, v, vr, nullptr);
-      xca_put<T, D>(dr, s_a);
-      xca_put<T, D>(vr, s_b);
-    }
-    __syncthreads();
-    for (int r = 0; r < nr; ++r) {
-      const float x = s_a[r][e];
-#pragma unroll
-      for (int u = 0; u < EPT; ++u) da[u] += x * s_b[r][c0 + u];
-    }
-    for (int r = r3; r < nr; r += RPP) {
-      const int32_t row = s_row[r];
-      float s = 0.f;
-#pragma unroll
-      for (int j = 0; j < D; j += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(&s_a[r][j]);
-        s += acl[j] * x.x + acl[j + 1] * x.y + acl[j + 2] * x.z + acl[j + 3] * x.w;
-      }
-      if (row >= 0) XcaIo<T>::store(dv + (size_t)row * rs + col + x3, s);
-    }
-  }
-
-  // 3. dG and the temperature partial
-  float rsum = 0.f;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) rsum += a[u] * da[u];
-#pragma unroll
-  for (int m = 1; m < CPR; m <<= 1) rsum += __shfl_xor(rsum, m, 64);
-  float dg[EPT], pt = 0.f, srow = 0.f;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    dg[u] = a[u] * (da[u] - rsum);
-    pt += dg[u] * nn[u];
-  }
-  srow = pt;
-#pragma unroll
-  for (int m = 1; m < CPR; m <<= 1) srow += __shfl_xor(srow, m, 64);   // sum_c dG N over row e
-  // the workgroup's sum of dG * N: the rows' sums, wave by wave, in order
-  float wsum = (tid - e * CPR) == 0 ? srow : 0.f;
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) wsum += __shfl_xor(wsum, m, 64);
-  __syncthreads();   // the last block's readers of s_a, s_b and every reader of s_g (A,
-                     // whose place B_q takes) are done
-  if ((tid & 63) == 0) s_red[tid >> 6] = wsum;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    s_bq[e][c0 + u] = t * dg[u] / s_nrm[D + c0 + u];
-    s_bk[c0 + u][e] = t * dg[u] / s_nrm[e];
-  }
-  __syncthreads();
-  if (tid == 0) {
-    float tot = 0.f;
-#pragma unroll
-    for (int j = 0; j < NW; ++j) tot += s_red[j];
-    part[b] = tot;
-  }
-
-  // 4. dqh[:, x3], dkh[:, x3] for rows r3, r3 + RPP, ... of each block, and their
-  //    projections on qhat[:, x3], khat[:, x3]
-  const float nq = s_nrm[x3], nk = s_nrm[D + x3];
-  constexpr int RPT = kXcaRows / RPP;   // rows of a block per thread
-  float gqr[RPT], gkr[RPT];
-  // dqh and dkh of this thread's rows of the block in LDS: rows B_q[x3] and
-  // B_k[x3] are read 4 columns at a time, outside the loop over the rows, so
-  // that only one slice of them is held in registers
-  auto grads = [&](int nr) {
-#pragma unroll
-    for (int m = 0; m < RPT; ++m) {
-      gqr[m] = 0.f;
-      gkr[m] = 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < D; j += 4) {
-      const float4 bq = *reinterpret_cast<const float4*>(&s_bq[x3][j]);
-      const float4 bk = *reinterpret_cast<const float4*>(&s_bk[x3][j]);
-#pragma unroll
-      for (int m = 0; m < RPT; ++m) {
-        const int r = r3 + RPP * m;
-        if (r < nr) {
-          const float4 kx = *reinterpret_cast<const float4*>(&s_b[r][j]);
-          const float4 qx = *reinterpret_cast<const float4*>(&s_a[r][j]);
-          gqr[m] += bq.x * kx.x + bq.y * kx.y + bq.z * kx.z + bq.w * kx.w;
-          gkr[m] += bk.x * qx.x + bk.y * qx.y + bk.z * qx.z + bk.w * qx.w;
-        }
-      }
-    }
-  };
-  auto fetch_qk = [&](int32_t p0, int nr) {
-    uint4 qr[NP], kr[NP];
-    xca_fetch<T, D>(pm, p0, nr, n, rs, col, q, qr, s_row);
-    xca_fetch<T, D>(pm, p0, nr, n, rs, col, k, kr, nullptr);
-    xca_put<T, D>(qr, s_a);
-    xca_put<T, D>(kr, s_b);
-  };
-  float ps = 0.f, pk = 0.f;   // this thread's share of s_x3 and t_x3, in row order
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    __syncthreads();
-    fetch_qk(p0, nr);
-    __syncthreads();
-    grads(nr);
-#pragma unroll
-    for (int m = 0; m < RPT; ++m) {
-      const int r = r3 + RPP * m;
-      if (r < nr) {
-        ps += (s_a[r][x3] / nq) * gqr[m];
-        pk += (s_b[r][x3] / nk) * gkr[m];
-      }
-    }
-  }
-  // s_x3 = the RPP shares in order (the floor makes the norm a constant: no projection)
-  s_sp[r3][x3] = ps;
-  s_sp[RPP + r3][x3] = pk;
-  __syncthreads();
-  if (tid < 2 * D) {
-    const int c = tid & (D - 1), which = tid / D;
-    float x = 0.f;
-#pragma unroll
-    for (int j = 0; j < RPP; ++j) x += s_sp[which * RPP + j][c];
-    s_st[tid] = s_nrm[tid] > 1e-12f ? x : 0.f;
-  }
-  __syncthreads();
-  const float sq = s_st[x3], tk = s_st[D + x3];
-
-  // 5. dq[:, x3] and dk[:, x3]; a window of one block still has its q, k rows in
-  //    LDS and its dqh, dkh in registers
-  const bool one_block = re - rb <= kXcaRows;
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (!one_block) {
-      __syncthreads();
-      fetch_qk(p0, nr);
-      __syncthreads();
-      grads(nr);
-    }
-#pragma unroll
-    for (int m = 0; m < RPT; ++m) {
-      const int r = r3 + RPP * m;
-      if (r >= nr) continue;
-      const int32_t row = s_row[r];
-      if (row >= 0) {
-        XcaIo<T>::store(dq + (size_t)row * rs + col + x3, (gqr[m] - (s_a[r][x3] / nq) * sq) / nq);
-        XcaIo<T>::store(dk + (size_t)row * rs + col + x3, (gkr[m] - (s_b[r][x3] / nk) * tk) / nk);
-      }
-    }
-  }
-}
-
-// ---------------------------------------------- backward on the matrix cores
-// 16-bit storage, d = 32: the chain rule of k_xca_bwd with its contractions on
-// the matrix cores, the rows staged in LDS in their storage format, and the same
-// three passes (a window of one block stages all four matrices in the first).
-//   1. G tile (w / 2, w % 2) of wave w from transpose reads, as the forward;
-//      the norms and the softmax in fp32; A rounded to the storage type (bf16:
-//      high part and residual).
-//   2. dA = sum_r dout_r^T v_r, tile (w / 2, w % 2), from transpose reads; dv =
-//      dout A (dv[r][c] = sum_e A[e][c] dout[r][e]): A's columns by transpose
-//      reads, dout's rows as they lie; wave w forms rows 16w .. 16w + 15.
-//   3. dG and the temperature share in fp32 as before.  B_q[e][c] = tau dG[e][c]
-//      / nk_c spans the range of 1 / nk, which a floored norm (a zero column)
-//      makes 10^12 times wider than the rest, so the column factor is split:
-//      B_q[e][c] k[r][c] = (tau dG[e][c] s_c / nk_c) (k[r][c] / s_c) with s_c =
-//      2^floor(log2 nk_c).  The first factor (within [1/2, 1] of tau dG) is
-//      scaled by one power of two into [1, 2) and stored as high part and
-//      residual (16 bits in bf16, 22 in fp16, no overflow); the second is the
-//      staged row rescaled by a power of two (exact, |k / s_c| < 2).  B_k^T
-//      (B_k[c][e] = tau dG[e][c] / nq_e) alike with nq_e.
-//   4. dqh = k B_q^T and dkh = q B_k^T for rows 16w + i from row reads; the
-//      projections s_e and t_c summed from the same fp32 values over the rows
-//      (lanes, then waves, in a fixed order), so the one-row window's exact
-//      cancellation holds as in k_xca_bwd; then dq, dk.
-__device__ __forceinline__ float xca_pow2_scale(float x) {
-  if (!(x > 0.f) || !(x < 3.0e38f)) return 1.f;
-  const int ex = (int)((__float_as_uint(x) >> 23) & 0xffu) - 127;
-  return ldexpf(1.f, min(-ex, 126));
+//
+// Three passes over the window's rows: G, the norms and dA (one exchange for a
+// long window); dv and the projections (a second exchange); dq and dk, whose dqh
+// and dkh are formed again from registers rather than held (matrix products are
+// cheap here, registers are not).
+//
+// 16-bit storage: B_q[e][c] = tau dG[e][c] / nk_c spans the range of 1 / nk, and a
+// floored norm (a zero column) makes that 1e12 times wider than the rest.  So the
+// column factor is split: B_q[e][c] k[r][c] = (tau dG[e][c] s_c / nk_c)(k[r][c] /
+// s_c) with s_c = 2^floor(log2 nk_c).  The first factor, within [1/2, 1] of tau dG,
+// takes one power-of-two scale into [1, 2) and is carried as a high/residual pair;
+// the second is the row rescaled by a power of two, exactly, with |k / s_c| < 2.
+// B_k alike with nq.
+//
+// x / y for the normalised rows: the hardware reciprocal and one correction step,
+// exactly +-1 when x = +-y (a one-row window's only entry).
+__device__ __forceinline__ float xca_unit(float x, float y, float ry) {
+  const float h = x * ry;
+  return fmaf(fmaf(-h, y, x), ry, h);
 }
 
 // 2^floor(log2 x) for a normal x > 0 (the norms: at least 1e-12)
@@ -754,394 +492,370 @@ __device__ __forceinline__ float xca_pow2_floor(float x) {
   return __uint_as_float(__float_as_uint(x) & 0x7f800000u);
 }
 
-// A staged row's 8 channels 8g .. 8g + 7, each times a power of two (exact)
-template <typename T>
-__device__ __forceinline__ Raw<T, 8> xca_rescale(Raw<T, 8> x, const float (&m)[8]) {
-  Raw<T, 8> r;
+// A row's slots times powers of two (exact); fp32 rows stay as they are.
+template <typename T, int KS>
+__device__ __forceinline__ Raw<T, KS> xca_rescale(Raw<T, KS> x, const float (&nrm)[KS]) {
+  if constexpr (!Ty<T>::kNarrow) return x;
+  Raw<T, KS> r;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) r[j] = f32_to_u16<T>(u16_to_f32<T>(x[j]) * m[j]);
+  for (int j = 0; j < KS; ++j) {
+    // 1 / 2^e from the exponent bits: norms are normal numbers below 2^126
+    const float inv = __uint_as_float(0x7f000000u - (__float_as_uint(nrm[j]) & 0x7f800000u));
+    r[j] = f32_to_u16<T>(u16_to_f32<T>(x[j]) * inv);
+  }
   return r;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kXcaThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_xca_bwd_mma(
-    const PlanHeader* __restrict__ hdr, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ offs, const float* __restrict__ tau, const T* __restrict__ q,
-    const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ dout,
-    T* __restrict__ dq, T* __restrict__ dk, T* __restrict__ dv, float* __restrict__ part,
-    int32_t n, int32_t W, int32_t H) {
-  constexpr int D = 32;
-  constexpr int LDH = D + 8;
-  constexpr int EPT = D * D / kXcaThreads;
-  constexpr int CPR = D / EPT;
-  constexpr int NP = kXcaPerThread<T, D>;
-  constexpr int NW = kXcaThreads / 64;
-  constexpr bool kPair = std::is_same<T, bf16_t>::value;
-  using F = Frag<T, 8>;
-  static_assert(NP == 1 && kXcaPieces<T, D> == kXcaThreads, "one piece a thread");
-  __shared__ __align__(16) unsigned short s_q[kXcaRows][LDH];
-  __shared__ __align__(16) unsigned short s_k[kXcaRows][LDH];
-  __shared__ __align__(16) unsigned short s_d[kXcaRows][LDH];   // dout
-  __shared__ __align__(16) unsigned short s_v[kXcaRows][LDH];
-  // pass 2: [0] A, [1] its residual; from step 3: B_q and its residual
-  __shared__ __align__(16) unsigned short s_m[2][D][LDH];
-  // from step 3, in the place of the v rows (read last in pass 2): B_k^T and its
-  // residual
-  unsigned short (*const s_bk)[D][LDH] = reinterpret_cast<unsigned short (*)[D][LDH]>(&s_v[0][0]);
-  __shared__ float s_g[D][D + 1];     // G, then dA
-  __shared__ float s_nrm[2 * D];
-  __shared__ float s_sp[NW][2 * D];   // the waves' shares of s_e and t_c
-  __shared__ float s_st[2 * D];       // s_e, t_c
-  __shared__ float s_red[3][NW];      // temperature shares; maxima of |B_q|, |B_k|
-  __shared__ int32_t s_row[kXcaRows];
-  const int tid = (int)threadIdx.x;
-  int32_t w, h;
-  xca_item(blockIdx.x, H, w, h);
-  if (w >= W) return;
-  const size_t b = (size_t)w * H + h;   // this (window, head)'s temperature partial
-  if (hdr->magic != kPlanMagic || hdr->n != n || hdr->num_windows != W) {
-    if (tid == 0) part[b] = 0.f;
-    return;
-  }
-  const int32_t* pm = hdr->csr ? nullptr : perm;
-  const int32_t rb = max(0, min(offs[w], n)), re = max(rb, min(offs[w + 1], n));
-  if (rb == re) {
-    if (tid == 0) part[b] = 0.f;
-    return;
-  }
-  const int lane = tid & 63, wv = tid >> 6;
-  const int i = lane & 15, g = lane >> 4;
-  const size_t rs = (size_t)H * D;
-  const int col = h * D;
-  const float t = tau[h];
-  const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-  const int pr = tid >> 2, pc = tid & 3;   // piece tid of a block: row tid / 4, channels 8 (tid % 4) ..
-  auto put = [&](unsigned short (*s)[LDH], uint4 x) { *reinterpret_cast<uint4*>(&s[pr][8 * pc]) = x; };
-  auto row_op = [&](const unsigned short (*s)[LDH], int r) {
-    return *reinterpret_cast<const Raw<T, 8>*>(&s[r][8 * g]);
-  };
-  const bool one = re - rb <= kXcaRows;
-  const int et = wv >> 1, ct = wv & 1;
-
-  // 1. G (raw sums) and the column norms
-  floatx4 gacc = zero;
-  float nrm = 0.f;
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (p0 != rb) __syncthreads();
-    {
-      uint4 qr[NP], kr[NP];
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, q, qr, s_row);
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, k, kr, nullptr);
-      if (one) {
-        uint4 dr[NP], vr[NP];
-        xca_fetch<T, D>(pm, p0, nr, n, rs, col, dout, dr, nullptr);
-        xca_fetch<T, D>(pm, p0, nr, n, rs, col, v, vr, nullptr);
-        put(s_d, dr[0]);
-        put(s_v, vr[0]);
+template <typename T, int D>
+struct XcaBwdOp {
+  static constexpr int NT = Geo<D>::NT, KS = Geo<D>::KS;
+  static constexpr int NL = Ty<T>::kNarrow ? NT : 1;
+  Raw<T, KS> bq[NT], bql[NL];   // scaled B_q: row e = 16 t + i, slots c (and residual)
+  Raw<T, KS> bk[NT], bkl[NL];   // scaled B_k^T: row c = 16 t + i, slots e
+  float iq, ik;                 // the scales' inverses
+  // dqh and dkh of a row by slots
+  __device__ __forceinline__ void grads(const Raw<T, KS>& qr, const Raw<T, KS>& kr, const float (&nq)[KS],
+                                        const float (&nk)[KS], float (&gq)[KS], float (&gk)[KS]) const {
+    using F = Frag<T, KS>;
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    const Raw<T, KS> kb = xca_rescale<T, KS>(kr, nk), qb = xca_rescale<T, KS>(qr, nq);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      floatx4 x = F::mma(bq[t], kb, zero), y = F::mma(bk[t], qb, zero);
+      if constexpr (Ty<T>::kNarrow) {
+        x = F::mma(bql[t], kb, x);
+        y = F::mma(bkl[t], qb, y);
       }
-      put(s_q, qr[0]);
-      put(s_k, kr[0]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      if (32 * ks >= nr) break;
-      gacc = F::mma(xca_cols<T, LDH>(s_q, 32 * ks, et, i, g), xca_cols<T, LDH>(s_k, 32 * ks, ct, i, g), gacc);
-    }
-    if (tid < D) {
-      for (int r = 0; r < nr; ++r) {
-        const float x = u16_to_f32<T>(s_q[r][tid]);
-        nrm += x * x;
-      }
-    } else if (tid < 2 * D) {
-      for (int r = 0; r < nr; ++r) {
-        const float x = u16_to_f32<T>(s_k[r][tid - D]);
-        nrm += x * x;
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) s_g[16 * et + 4 * g + j][16 * ct + i] = gacc[j];
-  if (tid < 2 * D) s_nrm[tid] = fmaxf(sqrtf(nrm), 1e-12f);
-  __syncthreads();
-  // N = G / (nq nk), A = softmax of tau N over c, thread (e, c0 .. c0 + EPT - 1)
-  const int e = tid / CPR, c0 = (tid - e * CPR) * EPT;
-  float nn[EPT], a[EPT];
-  {
-    float mx = -3.0e38f;
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      nn[u] = s_g[e][c0 + u] / (s_nrm[e] * s_nrm[D + c0 + u]);
-      a[u] = t * nn[u];
-      mx = fmaxf(mx, a[u]);
-    }
-#pragma unroll
-    for (int m = 1; m < CPR; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-    float sum = 0.f;
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      a[u] = expf(a[u] - mx);
-      sum += a[u];
-    }
-#pragma unroll
-    for (int m = 1; m < CPR; m <<= 1) sum += __shfl_xor(sum, m, 64);
-    const float inv = 1.f / sum;
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      a[u] *= inv;
-      const unsigned short hi = f32_to_u16<T>(a[u]);
-      s_m[0][e][c0 + u] = hi;
-      if constexpr (kPair) s_m[1][e][c0 + u] = f32_to_u16<T>(a[u] - u16_to_f32<T>(hi));
-    }
-  }
-  __syncthreads();
-
-  // 2. dA, and dv = dout A for rows 16 wv + i of each block
-  Raw<T, 8> at[2], atl[2];
-#pragma unroll
-  for (int t2 = 0; t2 < 2; ++t2) {
-    at[t2] = xca_cols<T, LDH>(s_m[0], 0, t2, i, g);
-    if constexpr (kPair) atl[t2] = xca_cols<T, LDH>(s_m[1], 0, t2, i, g);
-  }
-  floatx4 dacc = zero;
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (!one) {
-      __syncthreads();   // the previous block's readers of s_d, s_v, s_row are done
-      uint4 dr[NP], vr[NP];
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, dout, dr, s_row);
-      xca_fetch<T, D>(pm, p0, nr, n, rs, col, v, vr, nullptr);
-      put(s_d, dr[0]);
-      put(s_v, vr[0]);
-      __syncthreads();
-    }
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      if (32 * ks >= nr) break;
-      dacc = F::mma(xca_cols<T, LDH>(s_d, 32 * ks, et, i, g), xca_cols<T, LDH>(s_v, 32 * ks, ct, i, g), dacc);
-    }
-    if (16 * wv < nr) {
-      const int r = 16 * wv + i;
-      const Raw<T, 8> db = row_op(s_d, r);
-      const int32_t row = r < nr ? s_row[r] : -1;
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2) {
-        floatx4 d4 = F::mma(at[t2], db, zero);
-        if constexpr (kPair) d4 = F::mma(atl[t2], db, d4);
-        if (row >= 0) {
-          u16x4 pk;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) pk[j] = f32_to_u16<T>(d4[j]);
-          *reinterpret_cast<u16x4*>(dv + (size_t)row * rs + col + 16 * t2 + 4 * g) = pk;
-        }
-      }
-    }
-  }
-  // s_g's readers (the softmax) passed the barrier after it
-#pragma unroll
-  for (int j = 0; j < 4; ++j) s_g[16 * et + 4 * g + j][16 * ct + i] = dacc[j];
-  __syncthreads();   // also: every reader of A in s_m and of the v rows is done
-
-  // 3. dG, the temperature share, B_q and B_k^T
-  float bq[EPT], bk[EPT];
-  {
-    float da[EPT], rsum = 0.f;
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      da[u] = s_g[e][c0 + u];
-      rsum += a[u] * da[u];
-    }
-#pragma unroll
-    for (int m = 1; m < CPR; m <<= 1) rsum += __shfl_xor(rsum, m, 64);
-    float pt = 0.f, mq = 0.f, mk = 0.f;
-    const float nqe = s_nrm[e];
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      const float dg = a[u] * (da[u] - rsum);
-      const float nkc = s_nrm[D + c0 + u];
-      pt += dg * nn[u];
-      bq[u] = t * dg * (xca_pow2_floor(nkc) / nkc);
-      bk[u] = t * dg * (xca_pow2_floor(nqe) / nqe);
-      mq = fmaxf(mq, fabsf(bq[u]));
-      mk = fmaxf(mk, fabsf(bk[u]));
-    }
-    float srow = pt;
-#pragma unroll
-    for (int m = 1; m < CPR; m <<= 1) srow += __shfl_xor(srow, m, 64);   // sum_c dG N over row e
-    float wsum = (tid - e * CPR) == 0 ? srow : 0.f;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-      wsum += __shfl_xor(wsum, m, 64);
-      mq = fmaxf(mq, __shfl_xor(mq, m, 64));
-      mk = fmaxf(mk, __shfl_xor(mk, m, 64));
-    }
-    if (lane == 0) {
-      s_red[0][wv] = wsum;
-      s_red[1][wv] = mq;
-      s_red[2][wv] = mk;
-    }
-  }
-  __syncthreads();
-  float mq = 0.f, mk = 0.f;
-#pragma unroll
-  for (int j = 0; j < NW; ++j) {
-    mq = fmaxf(mq, s_red[1][j]);
-    mk = fmaxf(mk, s_red[2][j]);
-  }
-  const float sq_ = xca_pow2_scale(mq), sk_ = xca_pow2_scale(mk);
-  if (tid == 0) {
-    float tot = 0.f;
-#pragma unroll
-    for (int j = 0; j < NW; ++j) tot += s_red[0][j];
-    part[b] = tot;
-  }
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    const float xq = bq[u] * sq_, xk = bk[u] * sk_;
-    const unsigned short hq = f32_to_u16<T>(xq), hk = f32_to_u16<T>(xk);
-    s_m[0][e][c0 + u] = hq;
-    s_m[1][e][c0 + u] = f32_to_u16<T>(xq - u16_to_f32<T>(hq));
-    s_bk[0][c0 + u][e] = hk;
-    s_bk[1][c0 + u][e] = f32_to_u16<T>(xk - u16_to_f32<T>(hk));
-  }
-  __syncthreads();
-
-  // 4. dqh, dkh of rows 16 wv + i, their projections, then dq, dk
-  const float iq = 1.f / sq_, ik = 1.f / sk_;
-  float gq[2][4], gk[2][4];   // dqh[r][16 t2 + 4 g + j], dkh[r][16 t2 + 4 g + j]
-  // (the B operands, the norms and the column scales are read from LDS where they
-  // are used: held in registers they cost a fourth workgroup per CU)
-  auto grads = [&](int r) {
-    float ik8[8], iq8[8];   // 1 / s_c for this lane's channels 8g .. 8g + 7
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      ik8[j] = 1.f / xca_pow2_floor(s_nrm[D + 8 * g + j]);
-      iq8[j] = 1.f / xca_pow2_floor(s_nrm[8 * g + j]);
-    }
-    const Raw<T, 8> kb = xca_rescale<T>(row_op(s_k, r), ik8), qb = xca_rescale<T>(row_op(s_q, r), iq8);
-#pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2) {
-      const floatx4 x = F::mma(row_op(s_m[1], 16 * t2 + i), kb, F::mma(row_op(s_m[0], 16 * t2 + i), kb, zero));
-      const floatx4 y = F::mma(row_op(s_bk[1], 16 * t2 + i), qb, F::mma(row_op(s_bk[0], 16 * t2 + i), qb, zero));
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        gq[t2][j] = x[j] * iq;
-        gk[t2][j] = y[j] * ik;
+        gq[4 * t + j] = x[j] * iq;
+        gk[4 * t + j] = y[j] * ik;
       }
     }
-  };
-  auto fetch_qk = [&](int32_t p0, int nr) {
-    uint4 qr[NP], kr[NP];
-    xca_fetch<T, D>(pm, p0, nr, n, rs, col, q, qr, s_row);
-    xca_fetch<T, D>(pm, p0, nr, n, rs, col, k, kr, nullptr);
-    put(s_q, qr[0]);
-    put(s_k, kr[0]);
-  };
-  float ps[2][4] = {}, pk[2][4] = {};
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (!one) {
-      __syncthreads();
-      fetch_qk(p0, nr);
-      __syncthreads();
+  }
+};
+
+template <typename T, int D, bool PARTS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restrict__ q, const T* __restrict__ k,
+               const T* __restrict__ v, const T* __restrict__ dout, T* __restrict__ dq, T* __restrict__ dk,
+               T* __restrict__ dv, float* __restrict__ part) {
+  constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
+  constexpr int KT = XcaSums<D, true>::kTiles;
+  constexpr int SL = KT * 64 > kStageWave<D> / 4 ? KT * 64 : kStageWave<D> / 4;
+  constexpr bool NW = Ty<T>::kNarrow;
+  // fp32 at d = 32: rows held through a window's three passes leave one wave per
+  // SIMD (or 230 spilled registers); read again for each pass, two
+  constexpr bool kHold = NW || D == 16;
+  using F = Frag<T, KS>;
+  __shared__ floatx4 s_part[kWaves * SL];
+  __shared__ WaveMeta s_meta[kWaves];
+  __shared__ __align__(16) float s_norm[kWaves][kXcaNorm<D>];
+  const int lane = lane_id();
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const PlanHeader* hdr = a.hdr;
+  if (hdr->magic != kPlanMagic || hdr->n != a.n || hdr->num_windows != a.W) return;
+  const Items it = work_items<PARTS ? kXcaPartFill : 0, 3>(a, hdr);
+  const int32_t* perm = hdr->csr ? nullptr : a.perm;
+  const int i = lane & 15, g = lane >> 4;
+  const size_t rs = (size_t)a.H * D;
+  const int32_t n = a.n, G = gridDim.x;
+  const Sel<T, D> sel(i, g);
+  floatx4* const slot = s_part + wv * SL;
+  float* const stage = reinterpret_cast<float*>(slot);
+  float* const norms = s_norm[wv];
+  const T* const mats[4] = {k, v, q, dout};
+  constexpr unsigned kKQ = 5u, kKQD = 13u, kAll = 15u;
+  WaveMeta& meta = s_meta[wv];
+  const bool csr = perm == nullptr;
+  int32_t item = blockIdx.x;
+  WaveWork wc, wn;
+  {
+    const Slot s0 = item_slot(it, item, wv), s1 = item_slot(it, item + G, wv);
+    wc = decode_work(a, s0, slot_entry(a, s0), wv);
+    wn = decode_work(a, s1, slot_entry(a, s1), wv);
+  }
+  request_perm(wc, perm, meta.perm[0], lane);
+  request_perm(wn, perm, meta.perm[1], lane);
+  request_offs(wc, a, meta.offs[0], lane);
+  request_entry(a, item_slot(it, item + 2 * G, wv), &meta.ent[0], lane);
+  int par = 0;   // ring slot of the current item
+  while (item < it.total) {
+    const WaveWork ww = wc;
+    const int col = ww.h * D;
+    // a share of more than kBlockRows rows is streamed through the block; so is every
+    // window in fp32 at d = 32
+    const bool resident = kHold && ww.rb - ww.ra <= kBlockRows;
+    // the item's rows and windows, and the entry of the item after next, from LDS;
+    // then the requests ahead (see k_sla_fwd)
+    wait_vm();
+    BlockRows br;
+    block_rows_lds(br, ww, meta.perm[par], csr, lane);
+    Stream str;
+    stream_lds(str, ww, a, it, meta.offs[par], lane);
+    const WaveWork wnn = decode_work(a, item_slot(it, item + 2 * G, wv), lds_entry(&meta.ent[par]), wv);
+    wait_lgkm();
+    request_perm(wnn, perm, meta.perm[par], lane);
+    request_offs(wn, a, meta.offs[par ^ 1], lane);
+    request_entry(a, item_slot(it, item + 3 * G, wv), &meta.ent[par ^ 1], lane);
+    Block<T, D, 4> bk;
+    int32_t fa = INT32_MIN, fb = ww.rb;   // the rows of this item's windows
+    if constexpr (PARTS) str.rows(fa, fb);
+    if (kHold && ww.kind != 0) {
+      block_fetch<T, D, 4>(bk, br, ww.ra, fb, n, mats, kAll, rs, col, g, fa);
+      block_arrange<T, D, 4>(bk, kAll);
     }
-    const int r = 16 * wv + i;
-    if (16 * wv < nr) {
-      grads(r);
-      if (r < nr) {
+    const float th = tau[ww.h];
+    WinIter wi;
+    for (bool more = wi.first(ww, str); more; more = wi.next(ww, str)) {
+      const int32_t wa = wi.wc.ws, wb = wi.wc.we;
+      auto refetch = [&](int32_t base, unsigned which) {
+        BlockRows br;
+        block_rows(br, base, ww.rb, perm, lane);
+        block_fetch<T, D, 4>(bk, br, base, wb, n, mats, which, rs, col, g, wa);
+        block_arrange<T, D, 4>(bk, which);
+      };
+      auto load_norms = [&](float(&nq)[KS], float(&nk)[KS], float(&rq)[KS], float(&rk)[KS]) {
+        asm volatile("" ::: "memory");   // not hoisted out of the loops over rows
+        xca_slots<D>(norms, g, nq);
+        xca_slots<D>(norms + D, g, nk);
+        xca_slots<D>(norms + 2 * D, g, rq);
+        xca_slots<D>(norms + 3 * D, g, rk);
+      };
+      XcaBwdOp<T, D> op;
+      Raw<T, KS> at[NT], atl[NT];   // A^T: row c = 16 t + i, slots e
+      {
+        // pass 1: G, the norms, dA
+        XcaSums<D, true> su;
+        su.clear();
+        for (int32_t base = ww.ra; base < ww.rb; base += kBlockRows) {
+          if (!kHold || base != ww.ra) refetch(base, kAll);
 #pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2) {
-          const u16x4 qx = *reinterpret_cast<const u16x4*>(&s_q[r][16 * t2 + 4 * g]);
-          const u16x4 kx = *reinterpret_cast<const u16x4*>(&s_k[r][16 * t2 + 4 * g]);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            ps[t2][j] += (u16_to_f32<T>(qx[j]) / s_nrm[16 * t2 + 4 * g + j]) * gq[t2][j];
-            pk[t2][j] += (u16_to_f32<T>(kx[j]) / s_nrm[D + 16 * t2 + 4 * g + j]) * gk[t2][j];
+          for (int jj = 0; jj < kBlockJobs; ++jj) {
+            const int32_t r0 = base + kSliceRows * jj;
+            if (job_overlaps(r0, wa, wb)) xca_sums_seg<T, D, 4>(bk.j[jj], r0, wa, wb, i, g, sel, stage, su);
           }
         }
+        if (wi.shared) {
+          su.publish(slot, lane);
+          lds_barrier();
+          su.combine(s_part, SL, lane, wv, ww.pair);
+          lds_barrier();
+        }
+        xca_norms<T, D>(su, norms, lane, i, g);
+        floatx4 N[NT][NT];
+        xca_softmax<T, D, true>(su.M, norms, th, i, g, N);
+        State<D> tr;   // transposed through LDS
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+          for (int et = 0; et < NT; ++et) tr.M[ct][et] = su.M[ct][et];
+        transposed_operand<T, D, kXcaPair<T>>(tr, 1.f, stage, i, g, at, atl);
+        // dG (in P), the temperature share, B_q (in M) and B_k (in P)
+        float pt = 0.f, mq = 0.f, mk = 0.f;
+        float fk[KS];
+        {
+          float nk[KS];
+          xca_slots<D>(norms + D, g, nk);
+          xca_slots<D>(norms + 3 * D, g, fk);
+#pragma unroll
+          for (int r = 0; r < KS; ++r) fk[r] *= th * (NW ? xca_pow2_floor(nk[r]) : 1.f);
+        }
+#pragma unroll
+        for (int et = 0; et < NT; ++et) {
+          float rsum = 0.f;
+#pragma unroll
+          for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rsum += su.M[ct][et][j] * su.P[ct][et][j];
+          rsum = sum_groups(rsum);
+          const float fq = th * norms[2 * D + 16 * et + i] * (NW ? xca_pow2_floor(norms[16 * et + i]) : 1.f);
+#pragma unroll
+          for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float dg = su.M[ct][et][j] * (su.P[ct][et][j] - rsum);
+              pt += dg * N[ct][et][j];
+              su.M[ct][et][j] = dg * fk[4 * ct + j];
+              tr.M[ct][et][j] = dg * fq;
+              mq = fmaxf(mq, fabsf(su.M[ct][et][j]));
+              mk = fmaxf(mk, fabsf(tr.M[ct][et][j]));
+            }
+        }
+        pt = sum_groups(sum_rows16(pt));
+        // waves that share a window hold the same sum; the first of them writes it
+        if (lane == 0 && ww.rb > ww.ra && (!wi.shared || (ww.pair ? (wv & 1) : wv) == 0))
+          part[(size_t)wi.window(ww) * a.H + ww.h] = pt;
+        const float sq = NW ? pow2_scale_to_one(wave_reduce<true>(mq)) : 1.f;
+        const float sk = NW ? pow2_scale_to_one(wave_reduce<true>(mk)) : 1.f;
+        op.iq = 1.f / sq;
+        op.ik = 1.f / sk;
+        xca_operand<T, D, NW>(su.M, sq, op.bq, op.bql);
+        transposed_operand<T, D, NW>(tr, sk, stage, i, g, op.bk, op.bkl);
+      }
+      // pass 2: dv, and the projections s_e, t_c by slots
+      float ps[KS], pk[KS];
+#pragma unroll
+      for (int r = 0; r < KS; ++r) ps[r] = pk[r] = 0.f;
+      for (int32_t base = ww.ra; base < ww.rb; base += kBlockRows) {
+        if (!resident) refetch(base, kKQD);
+#pragma unroll
+        for (int jj = 0; jj < kBlockJobs; ++jj)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const int32_t r0 = base + kSliceRows * jj;
+            if (!sub_overlaps(r0, s, wa, wb)) continue;
+            const int32_t row = r0 + 16 * s + i;
+            const auto& sb = bk.j[jj];
+            const bool in = sb.ok[s] && row >= wa && row < wb;
+            __builtin_amdgcn_sched_barrier(0);   // one sub-tile's operands live at a time
+            float x[KS];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+              floatx4 d4 = F::mma(at[t], sb.x[3][s], zero);
+              if constexpr (kXcaPair<T>) d4 = F::mma(atl[t], sb.x[3][s], d4);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) x[4 * t + j] = d4[j];
+            }
+            RowIO<T, D>::put(dv, row_off(sb.o[s], rs, col), g, F::from_f32(x), in);
+            float gq[KS], gk[KS], qf[KS], kf[KS], nq[KS], nk[KS], rq[KS], rk[KS];
+            load_norms(nq, nk, rq, rk);
+            op.grads(sb.x[2][s], sb.x[0][s], nq, nk, gq, gk);
+            F::to_f32(sb.x[2][s], qf);
+            F::to_f32(sb.x[0][s], kf);
+#pragma unroll
+            for (int r = 0; r < KS; ++r) {
+              ps[r] += in ? xca_unit(qf[r], nq[r], rq[r]) * gq[r] : 0.f;
+              pk[r] += in ? xca_unit(kf[r], nk[r], rk[r]) * gk[r] : 0.f;
+            }
+          }
+      }
+#pragma unroll
+      for (int r = 0; r < KS; ++r) {
+        ps[r] = sum_rows16(ps[r]);
+        pk[r] = sum_rows16(pk[r]);
+      }
+      if (wi.shared) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          slot[(2 * t) * 64 + lane] = floatx4{ps[4 * t], ps[4 * t + 1], ps[4 * t + 2], ps[4 * t + 3]};
+          slot[(2 * t + 1) * 64 + lane] = floatx4{pk[4 * t], pk[4 * t + 1], pk[4 * t + 2], pk[4 * t + 3]};
+        }
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < KS; ++r) ps[r] = pk[r] = 0.f;
+        const int w0 = ww.pair ? (wv & ~1) : 0, nw = ww.pair ? 2 : kWaves;
+        for (int w = w0; w < w0 + nw; ++w)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const floatx4 x = s_part[w * SL + (2 * t) * 64 + lane], y = s_part[w * SL + (2 * t + 1) * 64 + lane];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              ps[4 * t + j] += x[j];
+              pk[4 * t + j] += y[j];
+            }
+          }
+        lds_barrier();   // the slots may be written again
+      }
+      // a floored norm is a constant: no projection
+      {
+        float nq[KS], nk[KS];
+        xca_slots<D>(norms, g, nq);
+        xca_slots<D>(norms + D, g, nk);
+#pragma unroll
+        for (int r = 0; r < KS; ++r) {
+          ps[r] = nq[r] > kXcaFloor ? ps[r] : 0.f;
+          pk[r] = nk[r] > kXcaFloor ? pk[r] : 0.f;
+        }
+      }
+      // pass 3: dq, dk
+      for (int32_t base = ww.ra; base < ww.rb; base += kBlockRows) {
+        if (!resident) refetch(base, kKQ);
+#pragma unroll
+        for (int jj = 0; jj < kBlockJobs; ++jj)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const int32_t r0 = base + kSliceRows * jj;
+            if (!sub_overlaps(r0, s, wa, wb)) continue;
+            const int32_t row = r0 + 16 * s + i;
+            const auto& sb = bk.j[jj];
+            const bool in = sb.ok[s] && row >= wa && row < wb;
+            __builtin_amdgcn_sched_barrier(0);
+            float gq[KS], gk[KS], qf[KS], kf[KS], nq[KS], nk[KS], rq[KS], rk[KS];
+            load_norms(nq, nk, rq, rk);
+            op.grads(sb.x[2][s], sb.x[0][s], nq, nk, gq, gk);
+            F::to_f32(sb.x[2][s], qf);
+            F::to_f32(sb.x[0][s], kf);
+#pragma unroll
+            for (int r = 0; r < KS; ++r) {
+              const float xq = gq[r] - xca_unit(qf[r], nq[r], rq[r]) * ps[r];
+              const float xk = gk[r] - xca_unit(kf[r], nk[r], rk[r]) * pk[r];
+              gq[r] = NW ? xq * rq[r] : xca_unit(xq, nq[r], rq[r]);
+              gk[r] = NW ? xk * rk[r] : xca_unit(xk, nk[r], rk[r]);
+            }
+            RowIO<T, D>::put(dq, row_off(sb.o[s], rs, col), g, F::from_f32(gq), in);
+            RowIO<T, D>::put(dk, row_off(sb.o[s], rs, col), g, F::from_f32(gk), in);
+          }
       }
     }
-  }
-  // the rows' shares: over the 16 lanes of a group (rows 16 wv + i), then the waves
-#pragma unroll
-  for (int m = 1; m < 16; m <<= 1)
-#pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        ps[t2][j] += __shfl_xor(ps[t2][j], m, 64);
-        pk[t2][j] += __shfl_xor(pk[t2][j], m, 64);
-      }
-  if (i == 0) {
-#pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        s_sp[wv][16 * t2 + 4 * g + j] = ps[t2][j];
-        s_sp[wv][D + 16 * t2 + 4 * g + j] = pk[t2][j];
-      }
-  }
-  __syncthreads();
-  if (tid < 2 * D) {
-    float x = 0.f;
-#pragma unroll
-    for (int j = 0; j < NW; ++j) x += s_sp[j][tid];
-    s_st[tid] = s_nrm[tid] > 1e-12f ? x : 0.f;   // a floored norm is a constant: no projection
-  }
-  __syncthreads();
-  float sv[2][4], tv[2][4];
-#pragma unroll
-  for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      sv[t2][j] = s_st[16 * t2 + 4 * g + j];
-      tv[t2][j] = s_st[D + 16 * t2 + 4 * g + j];
-    }
-  for (int32_t p0 = rb; p0 < re; p0 += kXcaRows) {
-    const int nr = min(kXcaRows, re - p0);
-    if (!one) {
-      __syncthreads();
-      fetch_qk(p0, nr);
-      __syncthreads();
-    }
-    const int r = 16 * wv + i;
-    if (16 * wv >= nr) continue;
-    if (!one) grads(r);
-    const int32_t row = r < nr ? s_row[r] : -1;
-    if (row < 0) continue;
-#pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2) {
-      const u16x4 qx = *reinterpret_cast<const u16x4*>(&s_q[r][16 * t2 + 4 * g]);
-      const u16x4 kx = *reinterpret_cast<const u16x4*>(&s_k[r][16 * t2 + 4 * g]);
-      u16x4 oq, ok;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float nq = s_nrm[16 * t2 + 4 * g + j], nk = s_nrm[D + 16 * t2 + 4 * g + j];
-        oq[j] = f32_to_u16<T>((gq[t2][j] - (u16_to_f32<T>(qx[j]) / nq) * sv[t2][j]) / nq);
-        ok[j] = f32_to_u16<T>((gk[t2][j] - (u16_to_f32<T>(kx[j]) / nk) * tv[t2][j]) / nk);
-      }
-      *reinterpret_cast<u16x4*>(dq + (size_t)row * rs + col + 16 * t2 + 4 * g) = oq;
-      *reinterpret_cast<u16x4*>(dk + (size_t)row * rs + col + 16 * t2 + 4 * g) = ok;
-    }
+    item += G;
+    wc = wn;
+    wn = wnn;
+    par ^= 1;
   }
 }
 
-// dtau[h] = sum over windows, in window order, of the (window, head) partials:
-// 256 strided sums, then a fixed tree.
-__global__ __launch_bounds__(kXcaThreads) void k_xca_dtau(const float* __restrict__ part, int32_t W,
-                                                         int32_t H, float* __restrict__ dtau) {
-  __shared__ float s[kXcaThreads];
+// dtau[h] = sum over the windows that hold rows, in window order, of the (window,
+// head) partials: 256 strided sums, then a fixed tree.
+__global__ __launch_bounds__(256) void k_xca_dtau(KernelArgs a, const float* __restrict__ part,
+                                                  float* __restrict__ dtau) {
+  __shared__ float s[256];
   const int h = (int)blockIdx.x, tid = (int)threadIdx.x;
   float x = 0.f;
-  for (int32_t w = tid; w < W; w += kXcaThreads) x += part[(size_t)w * H + h];
+  if (a.hdr->magic == kPlanMagic && a.hdr->n == a.n && a.hdr->num_windows == a.W)
+#pragma unroll 4
+    for (int32_t w = tid; w < a.W; w += 256) {
+      const bool live = max(0, min(a.offs[w], a.n)) < min(a.offs[w + 1], a.n);
+      const float y = part[(size_t)w * a.H + h];
+      x += live ? y : 0.f;
+    }
   s[tid] = x;
   __syncthreads();
-  for (int m = kXcaThreads / 2; m > 0; m >>= 1) {
+  for (int m = 128; m > 0; m >>= 1) {
     if (tid < m) s[tid] += s[tid + m];
     __syncthreads();
   }
   if (tid == 0) dtau[h] = s[0];
+}
+
+// fp32 scenes of fewer rows per window slot than this take the vector-unit kernels
+// (sla_xca_vec.hip): a thin window costs a wave of the matrix-core kernels its whole
+// chain of fp32 products.  Forward + backward, H = 4, d = 32, 1,521 windows (us, vector
+// units against matrix cores): 10k rows 78 / 113, 25k 108 / 135, 60k 193 / 158; 612
+// log-normal windows, 30k rows: 524 / 172.
+constexpr int64_t kXcaVecRows = 28;
+
+template <typename T>
+bool xca_vec(int32_t n, int32_t W) {
+  return !Ty<T>::kNarrow && (int64_t)n < kXcaVecRows * W;
+}
+
+template <typename T, int D>
+hipError_t xca_impl(const void* plan, int32_t n, int32_t W, int32_t H, const float* tau,
+                    const void* q, const void* k, const void* v, void* o, hipStream_t stream) {
+  if constexpr (!Ty<T>::kNarrow)
+    if (xca_vec<T>(n, W))
+      return launch_xca_vec_fwd(plan, n, W, H, D, tau, static_cast<const T*>(q), static_cast<const T*>(k),
+                                static_cast<const T*>(v), static_cast<T*>(o), stream);
+  const PlanLayout lay = plan_layout(n, W);
+  const KernelArgs a = kernel_args(plan, lay, n, W, H, 0.f);
+  const int grid = grid_size(reinterpret_cast<const void*>(&k_xca_fwd_mma<T, D, false>), lay, n, H);
+  const auto kern = parts_fit(grid, n, H, kXcaPartFill) ? &k_xca_fwd_mma<T, D, true> : &k_xca_fwd_mma<T, D, false>;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a, tau,
+                     static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
+                     static_cast<T*>(o));
+  return hipGetLastError();
 }
 
 template <typename T, int D>
@@ -1149,49 +863,29 @@ hipError_t xca_bwd_impl(const void* plan, int32_t n, int32_t W, int32_t H, const
                         const void* q, const void* k, const void* v, const void* dout, void* dq,
                         void* dk, void* dv, float* dtau, float* part, hipStream_t stream) {
   const PlanLayout lay = plan_layout(n, W);
-  const char* base = static_cast<const char*>(plan);
-  if constexpr (Ty<T>::kNarrow && D == 32)
-    hipLaunchKernelGGL((k_xca_bwd_mma<T>), dim3(xca_grid(W, H)), dim3(kXcaThreads), 0, stream,
-                       reinterpret_cast<const PlanHeader*>(base + lay.header),
-                       reinterpret_cast<const int32_t*>(base + lay.perm),
-                       reinterpret_cast<const int32_t*>(base + lay.offsets), tau,
-                       static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
-                       static_cast<const T*>(dout), static_cast<T*>(dq), static_cast<T*>(dk),
-                       static_cast<T*>(dv), part, n, W, H);
-  else
-  hipLaunchKernelGGL((k_xca_bwd<T, D>), dim3(xca_grid(W, H)), dim3(kXcaThreads), 0, stream,
-                     reinterpret_cast<const PlanHeader*>(base + lay.header),
-                     reinterpret_cast<const int32_t*>(base + lay.perm),
-                     reinterpret_cast<const int32_t*>(base + lay.offsets), tau,
-                     static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
-                     static_cast<const T*>(dout), static_cast<T*>(dq), static_cast<T*>(dk),
-                     static_cast<T*>(dv), part, n, W, H);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_xca_dtau, dim3((unsigned)H), dim3(kXcaThreads), 0, stream, part, W, H, dtau);
-  return hipGetLastError();
-}
-
-template <typename T, int D>
-hipError_t xca_impl(const void* plan, int32_t n, int32_t W, int32_t H, const float* tau,
-                    const void* q, const void* k, const void* v, void* o, hipStream_t stream) {
-  const PlanLayout lay = plan_layout(n, W);
-  const char* base = static_cast<const char*>(plan);
-  if constexpr (Ty<T>::kNarrow && D == 32) {
-    hipLaunchKernelGGL((k_xca_fwd_mma<T>), dim3(xca_grid(W, H)), dim3(kXcaThreads), 0, stream,
-                       reinterpret_cast<const PlanHeader*>(base + lay.header),
-                       reinterpret_cast<const int32_t*>(base + lay.perm),
-                       reinterpret_cast<const int32_t*>(base + lay.offsets), tau,
-                       static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
-                       static_cast<T*>(o), n, W, H);
-    return hipGetLastError();
+  const KernelArgs a = kernel_args(plan, lay, n, W, H, 0.f);
+  if (n > 0) {
+    hipError_t e = hipSuccess;
+    bool vec = false;
+    if constexpr (!Ty<T>::kNarrow) {
+      vec = xca_vec<T>(n, W);
+      if (vec)
+        e = launch_xca_vec_bwd(plan, n, W, H, D, tau, static_cast<const T*>(q), static_cast<const T*>(k),
+                               static_cast<const T*>(v), static_cast<const T*>(dout), static_cast<T*>(dq),
+                               static_cast<T*>(dk), static_cast<T*>(dv), part, stream);
+    }
+    if (!vec) {
+      const int grid = grid_size(reinterpret_cast<const void*>(&k_xca_bwd_mma<T, D, false>), lay, n, H);
+      const auto kern = parts_fit(grid, n, H, kXcaPartFill) ? &k_xca_bwd_mma<T, D, true> : &k_xca_bwd_mma<T, D, false>;
+      hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a,
+                         tau, static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
+                         static_cast<const T*>(dout), static_cast<T*>(dq), static_cast<T*>(dk),
+                         static_cast<T*>(dv), part);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_xca_fwd<T, D>), dim3(xca_grid(W, H)), dim3(kXcaThreads), 0, stream,
-                     reinterpret_cast<const PlanHeader*>(base + lay.header),
-                     reinterpret_cast<const int32_t*>(base + lay.perm),
-                     reinterpret_cast<const int32_t*>(base + lay.offsets), tau,
-                     static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
-                     static_cast<T*>(o), n, W, H);
+  hipLaunchKernelGGL(k_xca_dtau, dim3((unsigned)H), dim3(256), 0, stream, a, part, dtau);
   return hipGetLastError();
 }
 
