@@ -572,8 +572,8 @@ hipError_t launch_cwi_forward(const int32_t* map, int32_t gx, int32_t gy, int32_
 //  * dx: with unique voxels, q is p's neighbour at +o exactly when p is q's at -o,
 //    so dx is the forward applied to dy with every kernel reversed (flip); the
 //    identity quarter passes dy through.
-//  * dw: k_cwi_dw.  A lane owns one (tap, 16-byte piece) pair of a branch, so
-//    its fp32 sums are one piece (8 fp16 or 4 fp32 channels) and no sums are
+//  * dw, fp32 (16-bit storage: k_cwi_dw_mma below): k_cwi_dw.  A lane owns one (tap, 16-byte piece) pair of a branch, so
+//    its fp32 sums are one piece (4 channels) and no sums are
 //    exchanged between lanes: a wave covers 64 pairs (the 13 taps x 4 pieces
 //    of a 32-channel fp16 branch fit one wave) and walks a contiguous range of
 //    rows, kDwBatch rows at a time with all their loads in flight (a row's
@@ -586,6 +586,22 @@ hipError_t launch_cwi_forward(const int32_t* map, int32_t gx, int32_t gy, int32_
 //    multiple of 8 and workgroup j of it takes row block (j mod 8) B / 8 + j / 8
 //    (B blocks), so each XCD walks one contiguous eighth of the rows for every
 //    branch and slice, and its L2 serves the lines they share.
+// Nonzero when a 16-byte piece of 16-bit values holds an infinity or NaN: adding one
+// to an exponent field of all ones carries into the sign's place.
+template <typename T>
+__device__ __forceinline__ uint32_t not_finite(uint4 v) {
+  constexpr uint32_t kOne = std::is_same<T, bf16_t>::value ? 0x00800080u : 0x04000400u;
+  constexpr uint32_t kMag = 0x7fff7fffu;
+  return (((v.x & kMag) + kOne) | ((v.y & kMag) + kOne) | ((v.z & kMag) + kOne) | ((v.w & kMag) + kOne)) & 0x80008000u;
+}
+
+// Orders this wave's LDS accesses (its own lanes' exchange).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 constexpr int kDwWaves = 4;          // waves per workgroup: adjacent row ranges
 constexpr int kDwBatch = 8;          // rows whose loads are in flight together
 #ifndef SLA_CWI_DW_ROWS
@@ -711,6 +727,217 @@ __global__ __launch_bounds__(256) void k_cwi_dw(CwiArgs a, DwGrid g, const T* __
              s_red[3][lane * E + e];
 }
 
+// 16-bit storage: k_cwi_dw_mma.  dw[t][c] = sum_p dy[p][c] x[p + t][c] is the
+// diagonal of a 16 x 16 product over rows p, 32 at a time.  Fifteen sixteenths of
+// each product go unused, and it still costs less than a lane per (tap, piece),
+// which reads dy once per tap and leaves up to 60% of the lanes idle: here a lane is
+// (row, piece) of the tap's neighbours, SP pieces of 16 bytes a row, and dy is read
+// once.  A neighbour block goes through LDS (its rows as they come, 16-byte writes)
+// and comes back by columns (transpose loads).  The four waves of a workgroup walk
+// the same rows, wave w with taps w, w + 4, ..., kDwTaps / 4 of a slice of kDwTaps;
+// a block's rows and cells are staged in LDS once per kDwChunk rows.  A step's
+// neighbours are requested with the next step's table entries.
+// What bounds it is that chain of round trips, two a step of 32 rows.  Measured against
+// k_cwi_dw: 60k pillars, C = 128, fp16: 21.5 us against 23.9; 80k voxels of a grid 8
+// deep, C = 64, bf16, where a lane per (tap, piece) left 60% of the lanes idle: 24.2 us
+// against 35.5.
+// Slots of rows past the block are zero.  Rows without a neighbour at a tap meet a
+// zero there; a step whose dy holds an infinity or NaN masks dy per tap instead, so
+// that 0 x inf does not reach the sum (as the hit test of k_cwi_dw).
+constexpr int kDwTaps = 16;
+constexpr int kDwChunk = 256;
+
+inline DwGrid cwi_dw_mma_grid(int32_t n, int32_t c, int32_t kx, int32_t ky, int32_t gz) {
+  DwGrid g = cwi_dw_grid(n, c, 2, kx, ky, gz);   // blocks and rows; slices of taps here
+  const int pq = c / 8, slabs = (pq + 3) / 4;
+  const int taps[3] = {kx, ky, gz == 1 ? 9 : 27};
+  for (int b = 0; b < 3; ++b) g.slices[b] = (taps[b] + kDwTaps - 1) / kDwTaps * slabs;
+  return g;
+}
+
+template <typename T, int SP>
+__global__ __launch_bounds__(256) void k_cwi_dw_mma(CwiArgs a, DwGrid g, const T* __restrict__ x,
+                                                    const T* __restrict__ dy, float* __restrict__ partial) {
+  constexpr int E = 8;                          // channels per piece
+  constexpr int RPL = SP == 4 ? 16 : 32;        // rows per load
+  constexpr int LPS = 32 / RPL;                 // loads per step of 32 rows
+  constexpr int TPW = kDwTaps / kDwWaves;       // taps per wave
+  constexpr int CT = SP == 4 ? 2 : 1;           // 16-channel tiles
+  constexpr int RS = SP * E;                    // LDS row, elements
+  constexpr int BUF = 32 * RS + (SP == 1 ? 8 : 0);   // SP = 1: the tile's upper half reads on
+  typedef short v4s __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) unsigned short s_buf[kDwWaves][TPW + 1][BUF];   // neighbours per tap; dy
+  // a row (-1: none), its cell, its coordinate along the branch's axis, and its sides
+  // of the grid with a neighbouring cell
+  __shared__ int4 s_rows[kDwChunk];
+  // workgroups in [branch][slice: slab, taps][row block] order
+  int32_t b = (int32_t)blockIdx.x;
+  int branch = 0;
+  const int32_t n0 = g.slices[0] * g.blocks, n1 = n0 + g.slices[1] * g.blocks;
+  if (b >= n1) {
+    branch = 2;
+    b -= n1;
+  } else if (b >= n0) {
+    branch = 1;
+    b -= n0;
+  }
+  const int32_t slice = b / g.blocks, jb = b - slice * g.blocks;
+  const int32_t kb = (jb & 7) * (g.blocks >> 3) + (jb >> 3);
+  const int slabs = a.pq / SP, slab = slice % slabs, t0 = slice / slabs * kDwTaps;
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, gl = lane >> 4;
+  const int lr = lane / SP, pc = lane % SP;     // row and piece of this lane's loads
+  const bool act = lr < RPL;
+  const int taps = branch == 0 ? a.kx : (branch == 1 ? a.ky : (a.gz == 1 ? 9 : 27));
+  const int half = branch == 0 ? (a.kx - 1) / 2 : (branch == 1 ? (a.ky - 1) / 2 : 0);
+  const int base = branch == 0 ? 0 : (branch == 1 ? a.kx : a.kx + a.ky);
+  // rows are 2^rsh pieces long; this lane's piece of a row
+  const int rsh = 31 - __builtin_clz(4 * a.pq);
+  const uint32_t pcol = (uint32_t)(branch * a.pq + slab * SP + pc);
+  const uint4* const xp = reinterpret_cast<const uint4*>(x);
+  const uint4* const dp = reinterpret_cast<const uint4*>(dy);
+  // this wave's taps: offset in cells, offset along the axis (valid while 0 <= coordinate
+  // + offset < lim) and the sides the offset needs (3 x 3 x 3, visited in-plane first)
+  const int lim = branch == 0 ? a.gx : (branch == 1 ? a.gy : 1);
+  int dc[TPW], da[TPW], side[TPW];
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) {
+    const int t = t0 + wave + kDwWaves * u;
+    const int k = branch == 2 ? (t + 9) % 27 : t;
+    const int ox = k % 3 - 1, oy = (k / 3) % 3 - 1, oz = k / 9 - 1;
+    da[u] = branch == 2 ? 0 : t - half;
+    dc[u] = branch == 0 ? t - half : (branch == 1 ? (t - half) * a.gx : (oz * a.gy + oy) * a.gx + ox);
+    side[u] = branch != 2 ? 0
+                          : (ox < 0 ? 1 : 0) | (ox > 0 ? 2 : 0) | (oy < 0 ? 4 : 0) | (oy > 0 ? 8 : 0) |
+                                (oz < 0 ? 16 : 0) | (oz > 0 ? 32 : 0);
+  }
+  const int nt = max(0, min(TPW, (taps - t0 - wave + kDwWaves - 1) / kDwWaves));
+  const int32_t r0 = min((int64_t)a.n, (int64_t)kb * kDwWaves * g.rows);
+  const int32_t r1 = min((int64_t)a.n, (int64_t)r0 + kDwWaves * g.rows);
+  floatx4 acc[TPW][CT];
+#pragma unroll
+  for (int u = 0; u < TPW; ++u)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[u][ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // columns 16 ct .. of a staged block: slot r of lane (i, gl) is row 8 gl + r
+  auto cols = [&](const unsigned short* s, int ct) -> Raw<T, 8> {
+    return lds_cols<T>(s, RS, 16 * ct, i, gl);
+  };
+  for (int32_t c0 = r0; c0 < r1; c0 += kDwChunk) {
+    const int cnt = min(kDwChunk, r1 - c0);
+    if (c0 != r0) __syncthreads();   // s_rows is free
+    {
+      int4 e = make_int4(-1, 0, 0, 0);
+      if (tid < cnt) {
+        const int32_t row = a.order ? a.order[c0 + tid] : c0 + tid;
+        if ((uint32_t)row < (uint32_t)a.n) {
+          const int32_t cx = a.coords[3 * row], cy = a.coords[3 * row + 1], cz = a.coords[3 * row + 2];
+          e = make_int4(row, (cz * a.gy + cy) * a.gx + cx, branch == 0 ? cx : (branch == 1 ? cy : 0),
+                        (cx > 0 ? 1 : 0) | (cx < a.gx - 1 ? 2 : 0) | (cy > 0 ? 4 : 0) | (cy < a.gy - 1 ? 8 : 0) |
+                            (cz > 0 ? 16 : 0) | (cz < a.gz - 1 ? 32 : 0));
+          // a row outside the grid has no neighbours
+          if ((uint32_t)cx >= (uint32_t)a.gx || (uint32_t)cy >= (uint32_t)a.gy || (uint32_t)cz >= (uint32_t)a.gz)
+            e.x = -1;
+        }
+      }
+      s_rows[tid] = e;
+    }
+    __syncthreads();
+    // table entries of the neighbours of rows q0 .. q0 + 31 as they come, and which of
+    // them count (bit u LPS + l of `in`; every load is unconditional, from a cell of
+    // the grid, and nothing here depends on its value: either would wait for it)
+    auto entries = [&](int q0, int32_t (&row)[LPS], int32_t (&nb)[TPW][LPS], uint32_t& in) {
+      in = 0;
+#pragma unroll
+      for (int l = 0; l < LPS; ++l) {
+        const int4 e = s_rows[q0 + l * RPL + (act ? lr : 0)];
+        row[l] = act ? e.x : -1;
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+          const bool ok = (u < nt) & (row[l] >= 0) & ((uint32_t)(e.z + da[u]) < (uint32_t)lim) &
+                          ((e.w & side[u]) == side[u]);
+          in |= (ok ? 1u : 0u) << (u * LPS + l);
+          nb[u][l] = a.map[ok ? e.y + dc[u] : 0];
+        }
+      }
+    };
+    auto masked = [](uint4 v, uint32_t m) { return make_uint4(v.x & m, v.y & m, v.z & m, v.w & m); };
+    int32_t row[LPS], nb[TPW][LPS];
+    uint32_t in;
+    entries(0, row, nb, in);
+    for (int q0 = 0; q0 < cnt; q0 += 32) {
+      uint4 dv[LPS], xv[TPW][LPS];
+      uint32_t hit[TPW][LPS];   // all ones where the neighbour exists
+#pragma unroll
+      for (int l = 0; l < LPS; ++l) {
+        dv[l] = dp[((uint32_t)max(row[l], 0) << rsh) + pcol];
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+          const bool h = ((in >> (u * LPS + l)) & 1) & ((uint32_t)nb[u][l] < (uint32_t)a.n);
+          hit[u][l] = h ? ~0u : 0u;
+          xv[u][l] = xp[(((uint32_t)nb[u][l] & hit[u][l]) << rsh) + pcol];
+        }
+      }
+      const bool dlive[2] = {row[0] >= 0, row[LPS - 1] >= 0};
+      entries(q0 + 32 < cnt ? q0 + 32 : 0, row, nb, in);
+      uint32_t odd = 0;   // a dy that is not finite
+#pragma unroll
+      for (int l = 0; l < LPS; ++l) {
+        dv[l] = masked(dv[l], dlive[l] ? ~0u : 0u);
+        odd |= not_finite<T>(dv[l]);
+        if (act) {
+          *reinterpret_cast<uint4*>(&s_buf[wave][TPW][(l * RPL + lr) * RS + pc * E]) = dv[l];
+#pragma unroll
+          for (int u = 0; u < TPW; ++u)
+            *reinterpret_cast<uint4*>(&s_buf[wave][u][(l * RPL + lr) * RS + pc * E]) = masked(xv[u][l], hit[u][l]);
+        }
+      }
+      wave_sync();
+      if (__ballot(odd != 0) == 0) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          const Raw<T, 8> A = cols(s_buf[wave][TPW], ct);
+#pragma unroll
+          for (int u = 0; u < TPW; ++u)
+            if (u < nt) acc[u][ct] = Frag<T, 8>::mma(A, cols(s_buf[wave][u], ct), acc[u][ct]);
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+          if (u >= nt) break;
+#pragma unroll
+          for (int l = 0; l < LPS; ++l)
+            if (act)
+              *reinterpret_cast<uint4*>(&s_buf[wave][TPW][(l * RPL + lr) * RS + pc * E]) =
+                  masked(dv[l], hit[u][l]);
+          wave_sync();
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            acc[u][ct] = Frag<T, 8>::mma(cols(s_buf[wave][TPW], ct), cols(s_buf[wave][u], ct), acc[u][ct]);
+          wave_sync();
+        }
+      }
+      wave_sync();   // the buffers are free
+    }
+  }
+  // the diagonals: lane (i, gl) with 4 gl <= i < 4 gl + 4 holds channel i in component i - 4 gl
+  const int32_t total = (a.kx + a.ky + 27) * a.c;
+  float* dst = partial + (size_t)kb * total + (size_t)slab * SP * E;
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) {
+    if (u >= nt) break;
+    const int t = t0 + wave + kDwWaves * u;
+    const int k = branch == 2 ? (t + 9) % 27 : t;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const int j = i & 3;
+      const float v = j < 2 ? (j == 0 ? acc[u][ct][0] : acc[u][ct][1]) : (j == 2 ? acc[u][ct][2] : acc[u][ct][3]);
+      if (gl == (i >> 2) && 16 * ct + i < RS) dst[(size_t)(base + k) * a.c + 16 * ct + i] = v;
+    }
+  }
+}
+
 // dw[i] = sum of the workgroups' partials, in workgroup order (16 interleaved
 // slices, then the slices in order).  The 3 x 3 x 3 taps off the plane of a
 // one-cell-deep grid are never visited: their gradients are zero.
@@ -751,14 +978,23 @@ size_t cwi_backward_workspace_bytes(int32_t n, int32_t channels, int32_t kx, int
 template <typename T>
 static hipError_t launch_dw(const CwiArgs& a, const DwGrid& g, const void* x, const void* dy,
                             float* partial, void* dw_x, void* dw_y, void* dw_3, hipStream_t stream) {
-  const unsigned grid = (unsigned)((g.slices[0] + g.slices[1] + g.slices[2]) * g.blocks);
-  hipLaunchKernelGGL((k_cwi_dw<T>), dim3(grid), dim3(256), 0, stream, a, g, static_cast<const T*>(x),
-                     static_cast<const T*>(dy), partial);
+  const T *xs = static_cast<const T*>(x), *ds = static_cast<const T*>(dy);
+  int32_t blocks = g.blocks;
+  if constexpr (std::is_same<T, float>::value) {
+    const unsigned grid = (unsigned)((g.slices[0] + g.slices[1] + g.slices[2]) * g.blocks);
+    hipLaunchKernelGGL((k_cwi_dw<T>), dim3(grid), dim3(256), 0, stream, a, g, xs, ds, partial);
+  } else {
+    const DwGrid m = cwi_dw_mma_grid(a.n, a.c, a.kx, a.ky, a.gz);
+    const auto kern = a.pq >= 4 ? &k_cwi_dw_mma<T, 4> : (a.pq == 2 ? &k_cwi_dw_mma<T, 2> : &k_cwi_dw_mma<T, 1>);
+    const unsigned grid = (unsigned)((m.slices[0] + m.slices[1] + m.slices[2]) * m.blocks);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, a, m, xs, ds, partial);
+    blocks = m.blocks;
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int32_t total = (a.kx + a.ky + 27) * a.c;
   hipLaunchKernelGGL((k_cwi_dw_reduce<T>), dim3((unsigned)((total + 63) / 64)), dim3(1024), 0, stream,
-                     partial, g.blocks, a.kx, a.ky, a.c, a.gz, static_cast<T*>(dw_x),
+                     partial, blocks, a.kx, a.ky, a.c, a.gz, static_cast<T*>(dw_x),
                      static_cast<T*>(dw_y), static_cast<T*>(dw_3));
   return hipGetLastError();
 }
