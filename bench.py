@@ -93,8 +93,8 @@ def kernel_source_hash():
 
 
 def short_kernel(name):
-    for k in ("k_sla_bwd", "k_sla_fwd_proj", "k_sla_fwd", "k_sort", "k_merge", "k_plan", "k_cwi_tiled",
-              "k_cwi_fwd", "k_cwi_dw_reduce", "k_cwi_dw", "k_cwi_map", "k_cwi_clear", "k_xca_fwd_mma",
+    for k in ("k_sla_bwd", "k_sla_fwd_proj", "k_sla_fwd", "k_sort", "k_offsets", "k_merge", "k_plan", "k_cwi_tiled",
+              "k_cwi_fwd", "k_cwi_dw_reduce", "k_cwi_dw_mma", "k_cwi_dw", "k_cwi_map", "k_cwi_clear", "k_xca_fwd_mma",
               "k_xca_bwd_mma", "k_xca_fwd", "k_xca_bwd", "k_xca_dtau", "k_out_proj", "k_rows_gemm",
               "k_wgrad_reduce", "k_wgrad", "k_prep"):
         if k in name:
@@ -134,7 +134,7 @@ def pmc_summary(fetch_csv, write_csv):
         f"write_factor: {fw:.4f}   (WRITE_SIZE bytes by the copy / bytes it writes)",
         "kernel      dispatches  FETCH_raw_B   WRITE_raw_B   fetch_scaled_B  write_scaled_B  traffic_scaled_B",
     ]
-    for k in ("k_sort", "k_merge", "k_plan", "k_sla_fwd", "k_sla_bwd", "k_cwi_clear", "k_cwi_map",
+    for k in ("k_sort", "k_offsets", "k_merge", "k_plan", "k_sla_fwd", "k_sla_bwd", "k_cwi_clear", "k_cwi_map",
               "k_cwi_tiled", "k_cwi_fwd", "k_cwi_dw", "k_cwi_dw_reduce", "copy"):
         if k in f and k in w:
             fr, wr = f[k][0], w[k][0]

@@ -13,11 +13,14 @@
 //            others take a range of windows each: offsets from the blocks' prefix
 //            rows, and every sorted position of the range filled from the run of
 //            the block it falls in.
+// With many (row, window) counts, three launches: k_sort without the totals, k_offsets
+// (the offsets as sums over the blocks' prefix rows), and k_merge; see use_totals.
 // No workgroup waits on another, and every sum is an integer sum, so the result
 // is deterministic.  The totals must be zero when a build starts: a new plan
 // buffer is zero-filled once, and every build leaves them zero.
 // Mode B (CSR offsets given) and n = 0: one workgroup, k_plan, validates the
 // offsets and writes the chunk table and header.
+#include <algorithm>
 #include <atomic>
 
 #include "sla_common.h"
@@ -502,8 +505,8 @@ __device__ __forceinline__ uint64_t lanemask_lt(int lane) {
 //   sorted[block E + p]   row at position p of the block's sorted order;
 //   counts[block][x]      rows of the block with key < x, x = 0..W (the start of
 //                         window x's run in the block's sorted order);
-// and adds its window counts (x = 0..W; x = W counts the ids outside [0, W)) to
-// the window totals, integer atomics, so the sums do not depend on their order.
+// and, TOTALS, adds its window counts (x = 0..W; x = W counts the ids outside [0, W))
+// to the window totals, integer atomics, so the sums do not depend on their order.
 // Both go out as soon as the histogram is complete, under the radix passes.
 // LDS: hist[ld] | buf[2][E] | wcnt[2][256][17] (one count table when R = 8).
 constexpr int kSortThreads = 1024;
@@ -527,7 +530,7 @@ __device__ __forceinline__ V block_exsum(V x, V* s) {
   return before + inc - x;
 }
 
-template <int R>
+template <int R, bool TOTALS>
 __global__ __launch_bounds__(kSortThreads) void k_sort(const int32_t* __restrict__ ids, int32_t n,
                                                       int32_t W, int32_t ld,
                                                       int32_t* __restrict__ counts,
@@ -616,7 +619,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort(const int32_t* __restrict
         const int32_t c = hist[x];
         row[x] = h;
         h += c;
-        if (c) __hip_atomic_fetch_add(totals + x, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (TOTALS && c) __hip_atomic_fetch_add(totals + x, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
     lds_sync();
@@ -642,10 +645,37 @@ __global__ __launch_bounds__(kSortThreads) void k_sort(const int32_t* __restrict
   }
 }
 
+// ---------------------------------------------------------------- k_offsets
+// offsets[x] = sum over blocks of counts[b][x] (rows with a window id below x), x = 0..W:
+// 64 columns a workgroup, wave u summing blocks u, u + 16, ..., eight loads in flight.
+constexpr int kOffsetsThreads = 1024;
+
+__global__ __launch_bounds__(kOffsetsThreads) void k_offsets(int32_t W, int32_t nb, int32_t ld,
+                                                             const int32_t* __restrict__ counts,
+                                                             int32_t* __restrict__ plan_offsets,
+                                                             int32_t* __restrict__ offsets_out) {
+  __shared__ int32_t s[kOffsetsThreads / 64][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int32_t x = (int32_t)blockIdx.x * 64 + lane;
+  int32_t sum = 0;
+  if (x <= W) {
+#pragma unroll 8
+    for (int32_t b = wv; b < nb; b += kOffsetsThreads / 64) sum += counts[(size_t)b * ld + x];
+  }
+  s[wv][lane] = sum;
+  lds_sync();
+  if (wv != 0 || x > W) return;
+  int32_t total = 0;
+#pragma unroll
+  for (int u = 0; u < kOffsetsThreads / 64; ++u) total += s[u][lane];
+  plan_offsets[x] = total;
+  if (offsets_out) offsets_out[x] = total;
+}
+
 // ------------------------------------------------------------------ k_merge
-// Workgroup 0 writes the offsets (the exclusive scan of the window totals), the
-// chunk and long-window tables and the header, and clears the totals for the next
-// build.  Workgroup 1 + r takes the range of ww windows [w0, w0 + nx): from the
+// Workgroup 0 writes the chunk and long-window tables and the header: TOTALS, from the
+// window totals, whose exclusive scan it writes as the offsets, clearing them for the
+// next build; otherwise from the offsets k_offsets wrote.  Workgroup 1 + r takes the range of ww windows [w0, w0 + nx): from the
 // blocks' prefix rows (counts[b][x], x = w0..w0 + nx) it forms, per column x, the
 // exclusive sum over blocks ex[x][b] = sum_{b' < b} counts[b'][x]; ex[x][nb] is
 // offsets[x] (rows with a window id below x, over all blocks), and the rows of
@@ -656,6 +686,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort(const int32_t* __restrict
 // No workgroup waits for another.
 constexpr int kMergeThreads = 1024;
 
+template <bool TOTALS>
 __global__ __launch_bounds__(kMergeThreads) void k_merge(
     int32_t n, int32_t W, int32_t L, int32_t E, int32_t nb, int32_t ld, int32_t ww,
     const int32_t* __restrict__ counts, const int32_t* __restrict__ sorted,
@@ -673,8 +704,16 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(
     int32_t* s_off = lds;
     int32_t* s_aux = lds + (W + 1);
     int32_t n_long = 0, n_long4 = 0;
-    const int32_t n_chunks = tables_from_totals(totals, W, L, plan_offsets, offsets_out, s_off, s_aux, chunks,
-                                                longs, s_seg, s_scan2, &n_long, &n_long4, &s_invalid);
+    int32_t n_chunks;
+    if (TOTALS) {
+      n_chunks = tables_from_totals(totals, W, L, plan_offsets, offsets_out, s_off, s_aux, chunks, longs, s_seg,
+                                    s_scan2, &n_long, &n_long4, &s_invalid);
+    } else {
+      for (int w = tid; w <= W; w += kMergeThreads) s_off[w] = plan_offsets[w];
+      lds_sync();
+      if (tid == 0) s_invalid = n - s_off[W];
+      n_chunks = build_tables(s_off, s_aux, W, L, chunks, longs, s_scan, s_scan2, &n_long, &n_long4);
+    }
     lds_sync();
     if (tid == 0) write_header(hdr, n, W, L, n_chunks, n_long, n_long4, 0, s_invalid, invalid_out);
     return;
@@ -751,6 +790,17 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(
 }
 
 // ------------------------------------------------------------ host launchers
+// The totals cost one device-scope atomic per (block, window) that holds rows, up to
+// min(rows, blocks x windows) of them; without them k_offsets adds a launch and one
+// pass over the prefix rows.  Whole build, rows / windows, with the totals against
+// without (us): 60k / 1,521 12.8 / 15.8, 120k / 1,521 16.0 / 17.3, 480k / 256 (120k
+// counts) 21.9 / 22.9, 60k / 4,096 20.0 / 18.8, 120k / 3,042 22.2 / 20.4, 200k / 4,096
+// 33.4 / 25.3, 240k / 6,084 39.5 / 31.9, 480k / 12,168 71.1 / 51.7, 1M / 2,000 70.0 / 46.7.
+static bool use_totals(int64_t n, int64_t n_blocks, int64_t W) {
+  const int64_t counts = std::min(n, n_blocks * W);
+  return counts <= (W <= 2048 ? 160000 : 60000);
+}
+
 // Windows per merge workgroup: about 256 range workgroups, the tile within 96 KB.
 static int merge_windows(int32_t W, int32_t nb) {
   const int by_lds = (24 * 1024) / (nb + 1) - 1;
@@ -789,41 +839,41 @@ hipError_t launch_build(const int32_t* ids, int32_t n, int32_t W, int32_t L, int
   if (lay.n_blocks > kBuilderMaxBlocks) return hipErrorInvalidValue;
   // the dynamic LDS of both kernels may exceed the default limit: raise it once per
   // device (atomic: host threads may build plans concurrently; setting it twice is harmless)
-  static std::atomic<bool> attr_sort[4][64] = {}, attr_merge[64] = {};
+  static std::atomic<bool> attr_sort[2][4][64] = {}, attr_merge[2][64] = {};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
+  const bool tot = use_totals(n, lay.n_blocks, W);
   const int R = lay.block_elems / kSortThreads;
   const size_t sort_lds =
       ((size_t)lay.counts_ld + 2 * (size_t)lay.block_elems + (R <= 4 ? 2 : 1) * kDigits * kCountLd) * 4;
-  const dim3 sg(lay.n_blocks), st(kSortThreads);
+  const auto sort = [&](auto* kernel, int slot) {
+    const hipError_t err = raise_lds_limit(kernel, attr_sort[tot ? 1 : 0][slot], dev);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kernel, dim3(lay.n_blocks), dim3(kSortThreads), sort_lds, stream, ids, n, W, lay.counts_ld,
+                       counts, sorted, totals);
+    return hipGetLastError();
+  };
   switch (R) {
-    case 1:
-      if ((e = raise_lds_limit(&k_sort<1>, attr_sort[0], dev)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_sort<1>, sg, st, sort_lds, stream, ids, n, W, lay.counts_ld, counts, sorted, totals);
-      break;
-    case 2:
-      if ((e = raise_lds_limit(&k_sort<2>, attr_sort[1], dev)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_sort<2>, sg, st, sort_lds, stream, ids, n, W, lay.counts_ld, counts, sorted, totals);
-      break;
-    case 4:
-      if ((e = raise_lds_limit(&k_sort<4>, attr_sort[2], dev)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_sort<4>, sg, st, sort_lds, stream, ids, n, W, lay.counts_ld, counts, sorted, totals);
-      break;
-    case 8:
-      if ((e = raise_lds_limit(&k_sort<8>, attr_sort[3], dev)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_sort<8>, sg, st, sort_lds, stream, ids, n, W, lay.counts_ld, counts, sorted, totals);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case 1: e = sort(tot ? &k_sort<1, true> : &k_sort<1, false>, 0); break;
+    case 2: e = sort(tot ? &k_sort<2, true> : &k_sort<2, false>, 1); break;
+    case 4: e = sort(tot ? &k_sort<4, true> : &k_sort<4, false>, 2); break;
+    case 8: e = sort(tot ? &k_sort<8, true> : &k_sort<8, false>, 3); break;
+    default: return hipErrorInvalidValue;
   }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (e != hipSuccess) return e;
   const int ww = merge_windows(W, lay.n_blocks);
   const int groups = (W + ww - 1) / ww;
   const size_t tile = (size_t)(ww + 1) * (lay.n_blocks + 1), tables = 2 * ((size_t)W + 1);
   const size_t merge_lds = (tile > tables ? tile : tables) * 4;
-  if ((e = raise_lds_limit(&k_merge, attr_merge, dev)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_merge, dim3(groups + 1), dim3(kMergeThreads), merge_lds, stream, n, W, L,
+  if (!tot) {
+    hipLaunchKernelGGL(k_offsets, dim3(W / 64 + 1), dim3(kOffsetsThreads), 0, stream, W, lay.n_blocks,
+                       lay.counts_ld, counts, offs, offsets_io);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const auto merge = tot ? &k_merge<true> : &k_merge<false>;
+  if ((e = raise_lds_limit(merge, attr_merge[tot ? 1 : 0], dev)) != hipSuccess) return e;
+  hipLaunchKernelGGL(merge, dim3(groups + 1), dim3(kMergeThreads), merge_lds, stream, n, W, L,
                      lay.block_elems, lay.n_blocks, lay.counts_ld, ww, counts, sorted, totals, perm,
                      perm_out, offs, offsets_io, chunks, longs, hdr, invalid_out);
   return hipGetLastError();

@@ -44,3 +44,22 @@ def test_parts(sla, scene, dtype, H, d):  # noqa: F811
     # (fp32 XCA on windows this thin runs on the vector units, without parts)
     if scene != "one-row" and dtype != "f32":
         xca_backward_parity(sla, ids, None, n, W, q, k, v, do, _xca_tau(H), dtype, label=label)
+
+
+@pytest.mark.parametrize("n,W", [(60000, 2049), (60001, 2049), (160000, 2048), (160001, 2048), (160001, 7)])
+def test_builder_either_side_of_the_totals(sla, n, W):  # noqa: F811
+    # the builder sums its window counts with atomics up to a number of counts, and over
+    # the blocks' prefix rows above it: out-of-range ids, long windows and empty ones on
+    # both sides, the plan bit for bit, a buffer used twice
+    from tests.test_gpu_parity import check_plan
+    from tests.gpu_util import to_dev
+
+    rng = np.random.default_rng([72, n, W])
+    ids = np.minimum(rng.geometric(3.0 / W, size=n) - 1, W - 1).astype(np.int32)   # uneven: long windows first
+    ids[rng.random(n) < 0.01] = W + 5
+    ids[rng.random(n) < 0.01] = -1
+    plan = sla.build_segments(to_dev(ids), num_windows=W)
+    check_plan(sla, plan, ids, W, 0)
+    ids = ids[::-1].copy()
+    plan = sla.build_segments(to_dev(ids), num_windows=W, plan_buf=plan.buf)
+    check_plan(sla, plan, ids, W, 0)
