@@ -925,7 +925,10 @@ __device__ __forceinline__ void kgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
 //                windows and reads their rows only: a chunk of thin windows is a
 //                serial chain of up to 32 of them on one wave while the rest of the
 //                chip idles.  fp16 forward + backward (with the build), 1,521
-//                windows: 2k rows 110 -> 42 us, 6k rows 76 -> 56 us.
+//                windows: 2k rows 110 -> 42 us, 6k rows 76 -> 56 us; fp32 forward of
+//                1.9k rows in 64 windows 15.0 -> 12.0 us.  There are at most as many
+//                parts as window slots, twice that where they fill an eighth of the
+//                grid (at a third, 6k rows in 200 windows, it cost 16.5 -> 17.3 us).
 // Long items come first: they are the longest-running ones.
 //
 // Each wave software-pipelines its items: while item k computes, the plan entry
@@ -956,9 +959,14 @@ __device__ __forceinline__ Items work_items(const KernelArgs& a, const PlanHeade
   it.itemsL = it.itemsL4 + ((it.nL2 + 7) & ~7) * it.hp;
   const int32_t chunks = (it.nC + it.cpw - 1) / it.cpw * it.hg;
   it.part_bits = 0;
-  while (FILL > 0 && it.part_bits < BITS && (it.nC << (it.part_bits + 1)) <= a.W &&
-         (int64_t)chunks << (it.part_bits + 1) <= FILL * (int64_t)gridDim.x / 100)
+  while (FILL > 0 && it.part_bits < BITS) {
+    const int64_t items = (int64_t)chunks << (it.part_bits + 1);
+    if (items > FILL * (int64_t)gridDim.x / 100) break;
+    // parts without a window are cheap only while most of the grid is idle
+    const int64_t parts = (int64_t)it.nC << (it.part_bits + 1);
+    if (parts > (items <= (int64_t)gridDim.x / 8 ? 2 : 1) * (int64_t)a.W) break;
     ++it.part_bits;
+  }
   it.total = it.itemsL + (chunks << it.part_bits);
   return it;
 }
