@@ -25,10 +25,11 @@ namespace sla {
 // The output o ([n, C], original row order) then goes through the output
 // projection, k_out_proj.
 constexpr int kProjMaxC = 256;
-// Above this many 32-channel blocks (C > 128) a block's features are fetched and
-// projected one 32-row job at a time, so that at most one job's features are
-// live (64 VGPRs for C = 256, as both jobs' for C = 128).
-constexpr int kProjBlockFetchMaxCB = 4;
+// A block's features are fetched and projected one 32-row job at a time, so that
+// at most one job's features are live (8 VGPRs per 32 channels).  Both jobs' at once
+// took the bf16 kernels over 256 VGPRs and spilled 14 to 34 of them: 60k rows, C =
+// 128, with the output projection, 45.2 us against 50.7 at d = 32 and 48.4 against
+// 56.5 at d = 16; fp16, which did not spill, 43.0 against 43.4.
 
 struct ProjArgs {
   const void* x;  // [n, C] features
@@ -90,36 +91,6 @@ __device__ __forceinline__ Slot proj_slot(const ProjItems& it, int32_t item, int
     if (c < it.nC) sl.idx = c;
   }
   return sl;
-}
-
-// Feature rows of a block: lane (i, g) of sub-tile s of job jj holds channels
-// 32 kb + 8 g .. + 7 of its row for every 32-channel block kb.
-template <typename T, int CB>
-struct XBlock {
-  Raw<T, 8> x[kBlockJobs][2][CB];
-  int32_t o[kBlockJobs][2];
-  bool ok[kBlockJobs][2];
-};
-
-template <typename T, int CB>
-__device__ __forceinline__ void xblock_fetch(XBlock<T, CB>& xb, const BlockRows& br, int32_t base,
-                                             int32_t end, int32_t n, const T* x, int g) {
-  constexpr int C = 32 * CB;
-#pragma unroll
-  for (int jj = 0; jj < kBlockJobs; ++jj)
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const bool ok = (uint32_t)br.o[jj][s] < (uint32_t)n;
-      xb.ok[jj][s] = ok;
-      xb.o[jj][s] = ok ? br.o[jj][s] : 0;
-      const bool live = base + kSliceRows * jj + 16 * s < end;
-      const T* row = row_at(x, xb.o[jj][s], (size_t)C, 8 * g);
-#pragma unroll
-      for (int kb = 0; kb < CB; ++kb) {
-        if (live) xb.x[jj][s][kb] = __builtin_bit_cast(Raw<T, 8>, *reinterpret_cast<const uint4*>(row + 32 * kb));
-        else xb.x[jj][s][kb] = Frag<T, 8>::zero();
-      }
-    }
 }
 
 // The matrices selected by `which` (bit 0: K, 1: V, 2: Q) of one job's rows,
@@ -196,23 +167,6 @@ __device__ __forceinline__ void xjob_fetch(Raw<T, 8> (&xj)[2][CB], int32_t (&o)[
       if (live) xj[s][kb] = __builtin_bit_cast(Raw<T, 8>, *reinterpret_cast<const uint4*>(row + 32 * kb));
       else xj[s][kb] = Frag<T, 8>::zero();
     }
-  }
-}
-
-// All jobs of a block, job by job (a job's features are dead once its fragments
-// exist).
-template <typename T, int D, int CB>
-__device__ __forceinline__ void project(Block<T, D, 3>& bk, const XBlock<T, CB>& xb, unsigned which,
-                                        const T* s_w, const float* s_b, int i, int g) {
-#pragma unroll
-  for (int jj = 0; jj < kBlockJobs; ++jj) {
-    project_job<T, D, CB>(bk.j[jj], xb.x[jj], which, s_w, s_b, i, g);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      bk.j[jj].ok[s] = xb.ok[jj][s];
-      bk.j[jj].o[s] = xb.o[jj][s];
-    }
-    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -313,11 +267,6 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
     // streamed job by job: K, V for the state, then Q for the outputs.  The two
     // cases are separate branches, each with its own window loop, so that the
     // resident rows are not live in the streamed one.
-    constexpr bool kByJob = CB > kProjBlockFetchMaxCB;
-    XBlock<T, kByJob ? 1 : CB> xb;
-    if constexpr (!kByJob) {
-      if (ww.kind != 0 && resident) xblock_fetch<T, CB>(xb, cur.br, ww.ra, ww.rb, n, x, g);
-    }
     // the next item: its rows and windows are requested now, its successor's entry too
     Pending nxt;
     pending_request(nxt, a, nsl, ne, wv, perm, lane);
@@ -326,25 +275,15 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
     WinIter wi;
     if (resident) {
       Block<T, D, 3> bk;
-      if constexpr (kByJob) {
-        if (ww.kind != 0) {
 #pragma unroll
-          for (int jj = 0; jj < kBlockJobs; ++jj) {
-            Raw<T, 8> xj[2][CB];
-            xjob_fetch<T, CB>(xj, bk.j[jj].o, bk.j[jj].ok, cur.br, jj, ww.ra, ww.rb, n, x, g);
-            project_job<T, D, CB>(bk.j[jj], xj, kAll, s_w, s_b, i, g);
-            if constexpr (SAVE) save_job<T, D>(bk.j[jj], kAll, qkv, nC, rs, col, g);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      } else {
-        if (ww.kind != 0) {
-          project<T, D, CB>(bk, xb, kAll, s_w, s_b, i, g);
-          if constexpr (SAVE) {
-#pragma unroll
-            for (int jj = 0; jj < kBlockJobs; ++jj) save_job<T, D>(bk.j[jj], kAll, qkv, nC, rs, col, g);
-          }
-        }
+      for (int jj = 0; jj < kBlockJobs; ++jj) {
+        const int32_t r0 = ww.ra + kSliceRows * jj;
+        if (r0 >= ww.rb) continue;   // no window of the item reaches this job
+        Raw<T, 8> xj[2][CB];
+        xjob_fetch<T, CB>(xj, bk.j[jj].o, bk.j[jj].ok, cur.br, jj, ww.ra, ww.rb, n, x, g);
+        project_job<T, D, CB>(bk.j[jj], xj, kAll, s_w, s_b, i, g);
+        if constexpr (SAVE) save_job<T, D>(bk.j[jj], kAll, qkv, nC, rs, col, g);
+        __builtin_amdgcn_sched_barrier(0);
       }
       for (bool more = wi.first(ww, cur.str); more; more = wi.next(ww, cur.str)) {
         const int32_t wa = wi.wc.ws, wb = wi.wc.we;
