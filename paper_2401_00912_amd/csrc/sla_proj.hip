@@ -21,7 +21,9 @@ namespace sla {
 //   long items   (long window, head): four waves take quarters of a window of
 //                more than 2L rows; or (two long windows, head): waves 2m and
 //                2m + 1 take the halves of window m (L + 1 .. 2L rows);
-//   chunk items  (four chunks, head): one chunk per wave.
+//   chunk items  (four chunks, head): one chunk per wave; on small scenes a share
+//                of each chunk's windows (parts, as in the attention kernels), which
+//                projects the rows of its windows only.
 // The output o ([n, C], original row order) then goes through the output
 // projection, k_out_proj.
 constexpr int kProjMaxC = 256;
@@ -41,8 +43,10 @@ struct ProjArgs {
 struct ProjItems {
   int32_t nL, nL4, nL2p, nC, nCG, H;
   int32_t itemsL4, itemsL, total;
+  int32_t part_bits;
 };
 
+template <bool PARTS>
 __device__ __forceinline__ ProjItems proj_items(const KernelArgs& a, const PlanHeader* hdr) {
   ProjItems it;
   it.nL = max(0, min(hdr->n_long, a.max_long));
@@ -53,7 +57,11 @@ __device__ __forceinline__ ProjItems proj_items(const KernelArgs& a, const PlanH
   it.H = a.H;
   it.itemsL4 = ((it.nL4 + 7) & ~7) * a.H;
   it.itemsL = it.itemsL4 + ((it.nL2p + 7) & ~7) * a.H;
-  it.total = it.itemsL + ((it.nCG + 7) & ~7) * a.H;
+  it.part_bits = 0;
+  while (PARTS && it.part_bits < kMaxPartBits && (it.nC << (it.part_bits + 1)) <= a.W &&
+         ((int64_t)it.nCG << (it.part_bits + 1)) * a.H <= (int64_t)gridDim.x)
+    ++it.part_bits;
+  it.total = it.itemsL + (((it.nCG << it.part_bits) + 7) & ~7) * a.H;
   return it;
 }
 
@@ -67,6 +75,7 @@ __device__ __forceinline__ Slot proj_slot(const ProjItems& it, int32_t item, int
   sl.h = 0;
   sl.parts = 4;
   sl.piece = wv;
+  sl.part = 0;
   if (item >= it.total) return sl;
   const int32_t base = item < it.itemsL4 ? 0 : (item < it.itemsL ? it.itemsL4 : it.itemsL);
   const int32_t r = (item - base) >> 3;
@@ -86,7 +95,8 @@ __device__ __forceinline__ Slot proj_slot(const ProjItems& it, int32_t item, int
       sl.piece = wdx < nL2 ? (wv & 1) : -1;
     }
   } else {
-    const int32_t c = 4 * j + wv;
+    const int32_t c = 4 * (j >> it.part_bits) + wv;
+    sl.part = j & ((1 << it.part_bits) - 1);
     sl.table = 1;
     if (c < it.nC) sl.idx = c;
   }
@@ -222,7 +232,7 @@ __device__ __forceinline__ void stage_rows(T* s_w, float* s_b, const T* w, const
 
 // SAVE: q, k, v also go to pa.qkv as they are projected (for a backward that
 // does not recompute them).
-template <typename T, int D, int PHI, int CB, bool SAVE>
+template <typename T, int D, int PHI, int CB, bool SAVE, bool PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SLA_PROJ_WPE)))
 void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
   constexpr int KT = kStateTiles<D>, C = 32 * CB, LDW = C + 8;
@@ -233,7 +243,7 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const PlanHeader* hdr = a.hdr;
   if (hdr->magic != kPlanMagic || hdr->n != a.n || hdr->num_windows != a.W) return;
-  const ProjItems it = proj_items(a, hdr);
+  const ProjItems it = proj_items<PARTS>(a, hdr);
   const int head = ((int)blockIdx.x >> 3) % a.H;
   {
     const int32_t src[3] = {head * D, C + head * D, 2 * C + head * D};
@@ -273,12 +283,22 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
     nsl = proj_slot(it, item + 2 * G, wv);
     ne = slot_entry(a, nsl);
     WinIter wi;
+    int32_t fa = INT32_MIN, fb = ww.rb;   // the rows of this item's windows
+    if constexpr (PARTS) {
+      if (ww.kind == 1) {
+        cur.str.part = ww.part;
+        cur.str.bits = it.part_bits;
+        cur.str.rows(fa, fb);
+      }
+    }
     if (resident) {
       Block<T, D, 3> bk;
 #pragma unroll
       for (int jj = 0; jj < kBlockJobs; ++jj) {
-        const int32_t r0 = ww.ra + kSliceRows * jj;
-        if (r0 >= ww.rb) continue;   // no window of the item reaches this job
+        [[maybe_unused]] const int32_t r0 = ww.ra + kSliceRows * jj;
+        // a job that no window of the item reaches (the test costs large scenes at C =
+        // 256 two percent: 100.2 against 98.5 us on 60k rows)
+        if (PARTS && (r0 >= fb || r0 + kSliceRows <= fa)) continue;
         Raw<T, 8> xj[2][CB];
         xjob_fetch<T, CB>(xj, bk.j[jj].o, bk.j[jj].ok, cur.br, jj, ww.ra, ww.rb, n, x, g);
         project_job<T, D, CB>(bk.j[jj], xj, kAll, s_w, s_b, i, g);
@@ -437,15 +457,20 @@ static hipError_t proj_impl(const void* plan, int32_t n, int32_t W, int32_t H, f
   const PlanLayout lay = plan_layout(n, W);
   const KernelArgs a = kernel_args(plan, lay, n, W, H, eps);
   void (*fk)(KernelArgs, ProjArgs, T*) =
-      qkv ? &k_sla_fwd_proj<T, D, PHI, CB, true> : &k_sla_fwd_proj<T, D, PHI, CB, false>;
+      qkv ? &k_sla_fwd_proj<T, D, PHI, CB, true, false> : &k_sla_fwd_proj<T, D, PHI, CB, false, false>;
   const void* kern = reinterpret_cast<const void*>(fk);
   const int64_t c = resident_workgroups(kern);
   const int64_t unit = 8 * (int64_t)H;
   const int64_t ml = lay.max_long, mc = lay.max_chunks;
-  const int64_t items = (((ml + 7) & ~7) + (((ml + 1) / 2 + 7) & ~7) + (((mc + 3) / 4 + 7) & ~7)) * H;
+  int64_t items = (((ml + 7) & ~7) + (((ml + 1) / 2 + 7) & ~7) + (((mc + 3) / 4 + 7) & ~7)) * H;
   int64_t k = ((int64_t)n * H + c * kRowHeadsPerWorkgroup / 2) / (c * kRowHeadsPerWorkgroup);
   if (k < 1) k = 1;
   int64_t g = k * c;
+  // few chunks (fewer than kMaxChunkRows rows each) leave room for parts
+  if ((int64_t)n * 2 * H <= g * 4 * kMaxChunkRows) {
+    fk = qkv ? &k_sla_fwd_proj<T, D, PHI, CB, true, true> : &k_sla_fwd_proj<T, D, PHI, CB, false, true>;
+    items <<= kMaxPartBits;
+  }
   if (g > items) g = items;
   g = (g + unit - 1) / unit * unit;
   if (g < unit) g = unit;
