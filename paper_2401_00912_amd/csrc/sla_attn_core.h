@@ -1223,7 +1223,8 @@ __device__ __forceinline__ void pending_request(Pending& p, const KernelArgs& a,
   p.str.wp = p.ww.wb;
   p.str.a = p.str.b = 0;
   p.str.live = 0;
-  if (p.ww.kind != 0) block_rows(p.br, p.ww.ra, min(p.ww.rb, p.ww.ra + kBlockRows), perm, lane);
+  // an idle wave's item (no rows, ra = rb) gets -1 in every lane: no row is read or saved
+  block_rows(p.br, p.ww.ra, min(p.ww.rb, p.ww.ra + kBlockRows), perm, lane);
   if (p.ww.kind == 1) p.str.request(p.ww.wb);
 }
 

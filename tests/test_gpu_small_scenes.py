@@ -63,3 +63,31 @@ def test_builder_either_side_of_the_totals(sla, n, W):  # noqa: F811
     ids = ids[::-1].copy()
     plan = sla.build_segments(to_dev(ids), num_windows=W, plan_buf=plan.buf)
     check_plan(sla, plan, ids, W, 0)
+
+
+@pytest.mark.parametrize("rows", [60, 2003, 70001])
+@pytest.mark.parametrize("H,d", [(2, 32), (8, 32)])
+def test_saved_qkv_beside_idle_waves(sla, rows, H, d):  # noqa: F811
+    # the last chunk items leave waves without rows: with parts (few rows) and without
+    # (many), they store nothing into the saved q, k, v; rows of no window keep what
+    # the buffer held, the others hold the projection
+    import torch
+    from tests.gpu_util import to_dev
+
+    rng = np.random.default_rng([73, rows, H, d])
+    ids = rng.integers(0, max(1, rows // 37), size=rows).astype(np.int32)
+    ids[rng.random(rows) < 0.02] = -1
+    C = H * d
+    plan = sla.build_segments(to_dev(ids), num_windows=max(1, rows // 37))
+    gen = torch.Generator(device="cuda").manual_seed(73)
+    rand = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
+    x, wq, bq = (t.bfloat16() for t in (rand(rows, C), rand(3 * C, C) / C**0.5, 1.0 + rand(3 * C)))
+    wo = (rand(C, C) / C**0.5).bfloat16()
+    ref = torch.addmm(bq.float(), x.float(), wq.float().t()).reshape(rows, 3, C).transpose(0, 1)
+    inside = torch.from_numpy(ids >= 0).cuda()
+    for _ in range(3):
+        qkv = torch.full((3, rows, C), 7.0, dtype=torch.bfloat16, device="cuda")
+        sla.forward_projected(plan, x, wq, wo, H, bq, qkv_out=qkv)
+        assert torch.equal(qkv[:, ~inside], torch.full_like(qkv[:, ~inside], 7.0))
+        # half a bf16 step of the value, and fp32 sums of up to 256 products
+        assert (qkv.float() - ref).abs()[:, inside].le(ref.abs()[:, inside] * 2.0**-8 + 1e-4).all()
