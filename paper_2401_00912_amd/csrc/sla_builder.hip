@@ -792,13 +792,20 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(
 // ------------------------------------------------------------ host launchers
 // The totals cost one device-scope atomic per (block, window) that holds rows, up to
 // min(rows, blocks x windows) of them; without them k_offsets adds a launch and one
-// pass over the prefix rows.  Whole build, rows / windows, with the totals against
-// without (us): 60k / 1,521 12.8 / 15.8, 120k / 1,521 16.0 / 17.3, 480k / 256 (120k
-// counts) 21.9 / 22.9, 60k / 4,096 20.0 / 18.8, 120k / 3,042 22.2 / 20.4, 200k / 4,096
-// 33.4 / 25.3, 240k / 6,084 39.5 / 31.9, 480k / 12,168 71.1 / 51.7, 1M / 2,000 70.0 / 46.7.
+// pass over the prefix rows, while k_merge's table workgroup no longer scans the totals,
+// which grows with the windows.  Whole build, with the totals against without (us):
+//   windows   40k rows     60k rows     80k rows     120k rows    160k rows
+//    1,521    12.0 / 14.1  12.5 / 14.7  13.7 / 15.4  16.1 / 17.0  19.1 / 15.8
+//    2,025    13.5 / 14.9  14.1 / 15.6  15.1 / 16.4  17.3 / 17.8  19.5 / 16.5
+//    2,601    14.9 / 15.7  16.3 / 16.6  17.4 / 17.6  20.7 / 18.6  23.3 / 17.5
+//    3,042    15.3 / 16.1  16.9 / 17.0  18.1 / 17.8  21.5 / 18.9  24.1 / 17.8
+//    3,481    17.0 / 16.9  18.7 / 18.1  20.5 / 19.2  24.3 / 19.9  26.7 / 19.0
+//    6,084    20.0 / 19.4  22.2 / 21.0  24.3 / 22.4  28.2 / 23.2  30.7 / 23.0
+// at 10k rows 14.8 / 15.8 in 3,481 windows and 18.3 / 18.1 in 6,084; 480k rows in 256
+// (120k counts) 21.9 / 22.9; 1M in 2,000 70.0 / 46.7.
 static bool use_totals(int64_t n, int64_t n_blocks, int64_t W) {
   const int64_t counts = std::min(n, n_blocks * W);
-  return counts <= (W <= 2048 ? 160000 : 60000);
+  return counts <= (W <= 2048 ? 130000 : (W <= 3200 ? 75000 : (W <= 5000 ? 40000 : 10000)));
 }
 
 // Windows per merge workgroup: about 256 range workgroups, the tile within 96 KB.

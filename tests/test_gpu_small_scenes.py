@@ -46,7 +46,9 @@ def test_parts(sla, scene, dtype, H, d):  # noqa: F811
         xca_backward_parity(sla, ids, None, n, W, q, k, v, do, _xca_tau(H), dtype, label=label)
 
 
-@pytest.mark.parametrize("n,W", [(60000, 2049), (60001, 2049), (160000, 2048), (160001, 2048), (160001, 7)])
+@pytest.mark.parametrize("n,W", [(60000, 2049), (60001, 2049), (160000, 2048), (160001, 2048), (160001, 7), (130000, 2048),
+                                 (130001, 2048), (75000, 2049), (75001, 2049), (40000, 3201), (40001, 3201),
+                                 (10000, 5001), (10001, 5001)])
 def test_builder_either_side_of_the_totals(sla, n, W):  # noqa: F811
     # the builder sums its window counts with atomics up to a number of counts, and over
     # the blocks' prefix rows above it: out-of-range ids, long windows and empty ones on
