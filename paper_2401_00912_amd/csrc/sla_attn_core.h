@@ -1444,9 +1444,14 @@ inline int grid_size(const void* kernel, const PlanLayout& lay, int32_t n, int32
 // Whether a launch of `grid` workgroups may find its chunks too few for it (a chunk
 // holds fewer than kMaxChunkRows rows), so that parts are worth their code: the
 // kernels without them, one to two percent faster on larger scenes, run otherwise.
-inline bool parts_fit(int grid, int32_t n, int32_t H, int fill) {
+// work_items allows as many parts as window slots, so that two parts a chunk need
+// at most half as many chunks, n / kMaxChunkRows of them or more, as slots; or
+// twice that where they fill an eighth of the grid.
+inline bool parts_fit(int grid, int32_t n, int32_t W, int32_t H, int fill) {
   const int hw = H < 4 ? H : 4, cpw = 4 / hw, hg = (H + 3) / 4;
-  return (int64_t)n * hg * 2 * 100 <= (int64_t)grid * fill * kMaxChunkRows * cpw;
+  const int64_t items = (int64_t)n * hg * 2, room = (int64_t)grid * kMaxChunkRows * cpw;   // x kMaxChunkRows cpw
+  if ((int64_t)n * 2 > (int64_t)W * kMaxChunkRows && items * 8 > room) return false;
+  return items * 100 <= room * fill;
 }
 
 inline KernelArgs kernel_args(const void* plan, const PlanLayout& lay, int32_t n, int32_t W,

@@ -851,7 +851,7 @@ hipError_t xca_impl(const void* plan, int32_t n, int32_t W, int32_t H, const flo
   const PlanLayout lay = plan_layout(n, W);
   const KernelArgs a = kernel_args(plan, lay, n, W, H, 0.f);
   const int grid = grid_size(reinterpret_cast<const void*>(&k_xca_fwd_mma<T, D, false>), lay, n, H);
-  const auto kern = parts_fit(grid, n, H, kXcaPartFill) ? &k_xca_fwd_mma<T, D, true> : &k_xca_fwd_mma<T, D, false>;
+  const auto kern = parts_fit(grid, n, W, H, kXcaPartFill) ? &k_xca_fwd_mma<T, D, true> : &k_xca_fwd_mma<T, D, false>;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a, tau,
                      static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
                      static_cast<T*>(o));
@@ -876,7 +876,7 @@ hipError_t xca_bwd_impl(const void* plan, int32_t n, int32_t W, int32_t H, const
     }
     if (!vec) {
       const int grid = grid_size(reinterpret_cast<const void*>(&k_xca_bwd_mma<T, D, false>), lay, n, H);
-      const auto kern = parts_fit(grid, n, H, kXcaPartFill) ? &k_xca_bwd_mma<T, D, true> : &k_xca_bwd_mma<T, D, false>;
+      const auto kern = parts_fit(grid, n, W, H, kXcaPartFill) ? &k_xca_bwd_mma<T, D, true> : &k_xca_bwd_mma<T, D, false>;
       hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a,
                          tau, static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
                          static_cast<const T*>(dout), static_cast<T*>(dq), static_cast<T*>(dk),
@@ -944,8 +944,8 @@ static float* scratch_address(hipError_t& err) {
 }
 
 // sla_backward_xca with the dtau partials in `scratch` (num_windows * heads <=
-// kXcaScratchFloats, checked by the caller).  Every partial is written by every
-// call, so nothing is cleared.
+// kXcaScratchFloats, checked by the caller).  Every partial of a window with rows is
+// written by every call and no other one counts, so nothing is cleared.
 hipError_t launch_backward_xca_noalloc(const void* plan, int32_t n, int32_t W, int dtype, int32_t H, int32_t d,
                                        const float* tau, const void* q, const void* k, const void* v,
                                        const void* dout, void* dq, void* dk, void* dv, float* dtau,
