@@ -22,9 +22,10 @@
 // SIMD, as in k_sla_fwd / k_sla_bwd.  The kernels before held one 256-thread workgroup
 // per (window, head), whose 5 to 9 barriers and serial column sums set the time.
 // Kernel trace, one Waymo-like frame (60k rows, fp16, H = 4, d = 32): forward 24.0
-// us against 26.9, backward 56.5 against 85.9; forward + backward by events 79.9
-// against 105 us, 151 against 328 on 100k rows in log-normal windows (bf16), 73
-// against 140 at H = 8, d = 16 (which ran on the vector units).
+// us against 26.9, backward 56.5 against 85.9 on inputs used before; with ten sets in
+// turn, all from HBM, 29.1 against 28.4 and 67.6 against 87.6.  Forward + backward by
+// events 79.9 against 105 us, 151 against 328 on 100k rows in log-normal windows
+// (bf16), 73 against 140 at H = 8, d = 16 (which ran on the vector units).
 #include "sla.h"
 #include "sla_attn_core.h"
 
