@@ -907,68 +907,13 @@ __device__ __forceinline__ void kgrad_seg(const Slice<T, Geo<D>::KS, NM>& sb, in
 }
 
 
-// ------------------------------------------------------------- work items
-// A launch walks a list of work items; workgroup b takes items b, b + G, ...
-// (G = grid size, a multiple of 8, about the number of resident workgroups).
-// In order:
-//   long items   one per (long window, head): the four waves of the workgroup
-//                take a quarter of the window's rows each, add their partial
-//                states in LDS (in wave order, so every wave holds the same sum)
-//                and then form their rows' outputs.  Item numbers are laid out so
-//                that the heads of one window share an item residue mod 8, i.e.
-//                run on one XCD (workgroups are dealt to the 8 XCDs round-robin),
-//                where the L2 serves the other heads' halves of each row.
-//   chunk items  one per chunk and group of up to 4 heads (one wave per head;
-//                with fewer than 4 heads, several chunks share a workgroup).
-//                A scene whose items do not fill the grid splits every chunk into
-//                2^part_bits items, each of which takes a share of its non-empty
-//                windows and reads their rows only: a chunk of thin windows is a
-//                serial chain of up to 32 of them on one wave while the rest of the
-//                chip idles.  fp16 forward + backward (with the build), 1,521
-//                windows: 2k rows 110 -> 42 us, 6k rows 76 -> 56 us; fp32 forward of
-//                1.9k rows in 64 windows 15.0 -> 12.0 us.  There are at most as many
-//                parts as window slots, twice that where they fill an eighth of the
-//                grid (at a third, 6k rows in 200 windows, it cost 16.5 -> 17.3 us).
-// Long items come first: they are the longest-running ones.
-//
-// Each wave software-pipelines its items: while item k computes, the plan entry
-// of item k + 2 and the permutation entries and window offsets of item k + 1 are
-// in flight, so an item's row gathers start as soon as the previous item's rows
-// have been requested and its data path is one memory round trip long.
-struct Items {
-  int32_t nL4, nL2, nC, H, hp, hw, cpw, hg;
-  int32_t itemsL4, itemsL, total;
-  int32_t part_bits;
-};
-constexpr int kMaxPartBits = 4;
-
-// FILL: how many times the grid (in percent) the parts may fill; 0: no parts.
+// ------------------------------------------------------- work of a wave
+// FILL, BITS: as make_items.
 template <int FILL, int BITS = kMaxPartBits>
 __device__ __forceinline__ Items work_items(const KernelArgs& a, const PlanHeader* hdr) {
-  Items it;
   const int32_t nL = max(0, min(hdr->n_long, a.max_long));
-  it.nL4 = max(0, min(hdr->n_long4, nL));
-  it.nL2 = nL - it.nL4;
-  it.nC = max(0, min(hdr->n_chunks, a.max_chunks));
-  it.H = a.H;
-  it.hp = (a.H + 1) / 2;
-  it.hw = min(a.H, 4);
-  it.cpw = 4 / it.hw;
-  it.hg = (a.H + 3) / 4;
-  it.itemsL4 = ((it.nL4 + 7) & ~7) * a.H;
-  it.itemsL = it.itemsL4 + ((it.nL2 + 7) & ~7) * it.hp;
-  const int32_t chunks = (it.nC + it.cpw - 1) / it.cpw * it.hg;
-  it.part_bits = 0;
-  while (FILL > 0 && it.part_bits < BITS) {
-    const int64_t items = (int64_t)chunks << (it.part_bits + 1);
-    if (items > FILL * (int64_t)gridDim.x / 100) break;
-    // parts without a window are cheap only while most of the grid is idle
-    const int64_t parts = (int64_t)it.nC << (it.part_bits + 1);
-    if (parts > (items <= (int64_t)gridDim.x / 8 ? 2 : 1) * (int64_t)a.W) break;
-    ++it.part_bits;
-  }
-  it.total = it.itemsL + (chunks << it.part_bits);
-  return it;
+  const int32_t nL4 = max(0, min(hdr->n_long4, nL));
+  return make_items(nL4, nL - nL4, max(0, min(hdr->n_chunks, a.max_chunks)), a.H, a.W, (int32_t)gridDim.x, FILL, BITS);
 }
 
 struct WaveWork {
@@ -979,53 +924,6 @@ struct WaveWork {
   int pair;        // long window: 0 = the four waves share it, 1 = waves 2m, 2m + 1 do
   int part;        // chunk: which share of its windows
 };
-
-// Where item `item` puts wave wv (wave-uniform): table entry index (-1: none),
-// the table (0: long windows, 1: chunks), the head, and for a long window how
-// many waves share it and which share is this wave's (-1: none, the wave only
-// takes part in the workgroup's partial-state exchange).
-//   four-way long items: one per (window, head), the four waves take quarters;
-//   two-way long items: one per (window, pair of heads), waves 2m and 2m + 1
-//     take the halves of head 2 x (item's pair) + m.
-struct Slot {
-  int32_t idx;
-  int table, h, parts, piece, part;
-};
-
-__device__ __forceinline__ Slot item_slot(const Items& it, int32_t item, int wv) {
-  Slot sl;
-  sl.idx = -1;
-  sl.table = 0;
-  sl.h = 0;
-  sl.parts = 4;
-  sl.piece = wv;
-  sl.part = 0;
-  if (item >= it.total) return sl;
-  if (item < it.itemsL4) {
-    const int32_t r = item >> 3;
-    const int32_t j = (r / it.H) * 8 + (item & 7);
-    sl.h = r % it.H;
-    if (j < it.nL4) sl.idx = j;
-  } else if (item < it.itemsL) {
-    const int32_t r = (item - it.itemsL4) >> 3;   // itemsL4 is a multiple of 8
-    const int32_t j = (r / it.hp) * 8 + (item & 7);
-    const int h = (r % it.hp) * 2 + (wv >> 1);
-    sl.parts = 2;
-    sl.piece = h < it.H ? (wv & 1) : -1;
-    sl.h = h < it.H ? h : 0;
-    if (j < it.nL2) sl.idx = it.nL4 + j;
-  } else {
-    const int32_t bp = item - it.itemsL, b = bp >> it.part_bits;
-    sl.part = bp - (b << it.part_bits);
-    const int32_t grp = b / it.hg;
-    const int sub = wv / it.hw;
-    const int32_t c = grp * it.cpw + sub;
-    sl.table = 1;
-    sl.h = (b - grp * it.hg) * 4 + wv % it.hw;
-    if (sub < it.cpw && c < it.nC && sl.h < it.H) sl.idx = c;
-  }
-  return sl;
-}
 
 // The plan entry of a slot (4 ints; Chunk and LongWin have the same size).
 __device__ __forceinline__ int4 slot_entry(const KernelArgs& a, const Slot& sl) {
@@ -1439,19 +1337,6 @@ inline int grid_size(const void* kernel, const PlanLayout& lay, int32_t n, int32
   if (g > itemsL + (itemsC << kMaxPartBits)) g = itemsL + (itemsC << kMaxPartBits);
   g = (g + 7) & ~7;
   return (int)(g < 8 ? 8 : g);
-}
-
-// Whether a launch of `grid` workgroups may find its chunks too few for it (a chunk
-// holds fewer than kMaxChunkRows rows), so that parts are worth their code: the
-// kernels without them, one to two percent faster on larger scenes, run otherwise.
-// work_items allows as many parts as window slots, so that two parts a chunk need
-// at most half as many chunks, n / kMaxChunkRows of them or more, as slots; or
-// twice that where they fill an eighth of the grid.
-inline bool parts_fit(int grid, int32_t n, int32_t W, int32_t H, int fill) {
-  const int hw = H < 4 ? H : 4, cpw = 4 / hw, hg = (H + 3) / 4;
-  const int64_t items = (int64_t)n * hg * 2, room = (int64_t)grid * kMaxChunkRows * cpw;   // x kMaxChunkRows cpw
-  if ((int64_t)n * 2 > (int64_t)W * kMaxChunkRows && items * 8 > room) return false;
-  return items * 100 <= room * fill;
 }
 
 inline KernelArgs kernel_args(const void* plan, const PlanLayout& lay, int32_t n, int32_t W,

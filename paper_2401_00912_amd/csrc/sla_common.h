@@ -9,6 +9,8 @@
 
 #include <type_traits>
 
+#include "sla_items.h"
+
 namespace sla {
 
 // ----------------------------------------------------------------------------
@@ -19,7 +21,6 @@ namespace sla {
 constexpr int32_t kPlanMagic = 0x534c4132;   // "SLA2"
 constexpr int32_t kMaxWindows = 16384;       // LDS-resident window tables
 constexpr int32_t kMinChunkRows = 32;
-constexpr int32_t kMaxChunkRows = 64;        // rows one wavefront holds in registers
 constexpr int32_t kDefaultChunkRows = 64;
 
 struct PlanHeader {

@@ -1,0 +1,63 @@
+"""The schedule's integer arithmetic (csrc/sla_items.h), compiled for the host: every
+wave of every item gets a head of the tensor, also where it is idle (kernels index
+per-head arrays with it), and every share of a long window and every part of a chunk
+is some wave's exactly once."""
+from __future__ import annotations
+
+import subprocess
+
+import pytest
+
+from paper_2401_00912_amd.build import CSRC
+
+HARNESS = r"""
+#include "sla_items.h"
+#include <cstdio>
+#include <map>
+#include <tuple>
+using namespace sla;
+int main() {
+  const int heads[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 13, 16}, longs4[] = {0, 1, 9}, longs2[] = {0, 5, 8};
+  const int chunks[] = {0, 1, 3, 17, 64}, grids[] = {8, 512}, fills[] = {0, 100, 400};
+  for (int H : heads) for (int nL4 : longs4) for (int nL2 : longs2) for (int nC : chunks)
+  for (int grid : grids) for (int fill : fills) {
+    const Items it = make_items(nL4, nL2, nC, H, 200, grid, fill, kMaxPartBits);
+    std::map<std::tuple<int, int, int, int>, int> seen;
+    for (int item = 0; item < it.total + 2 * grid; ++item)
+      for (int wv = 0; wv < 4; ++wv) {
+        const Slot s = item_slot(it, item, wv);
+        if (s.h < 0 || s.h >= H) {
+          std::printf("H=%d nL4=%d nL2=%d nC=%d grid=%d item=%d wave=%d: head %d\n", H, nL4, nL2, nC, grid, item, wv, s.h);
+          return 1;
+        }
+        if (s.idx < 0 || s.piece < 0) continue;
+        if (s.idx >= (s.table == 0 ? nL4 + nL2 : nC)) return 2;
+        if (s.table == 0 && s.parts != (s.idx < nL4 ? 4 : 2)) return 3;
+        ++seen[std::make_tuple(s.table, s.idx, s.h, s.table == 0 ? s.piece : s.part)];
+      }
+    if ((int)seen.size() != H * (4 * nL4 + 2 * nL2 + (nC << it.part_bits))) return 4;
+    for (const auto& e : seen)
+      if (e.second != 1) return 5;
+  }
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def gxx(tmp_path_factory):
+    """Compile a harness against the kernels' host-checkable headers and run it."""
+    def run(source, *flags):
+        out = tmp_path_factory.mktemp("items")
+        (out / "harness.cc").write_text(source)
+        exe = str(out / "harness")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-D__host__=", "-D__device__=",
+                        "-D__forceinline__=inline", "-I", CSRC, *flags, str(out / "harness.cc"), "-o", exe],
+                       check=True, capture_output=True, text=True)
+        return subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    return run
+
+
+def test_every_wave_has_a_head_and_every_share_a_wave(gxx):
+    res = gxx(HARNESS)
+    assert res.returncode == 0, (res.returncode, res.stdout)
