@@ -253,7 +253,7 @@ __device__ __forceinline__ float xca_exp(float x) {
     return __builtin_amdgcn_exp2f(x * kLog2e);
   } else {
     constexpr float kLo = 1.925963033e-8f;   // log2 e - kLog2e
-    x = fmaxf(x, -128.f);                     // 2^-184 is zero
+    x = x < -128.f ? -128.f : x;              // 2^-184 is zero; a NaN stays one
     const float t = x * kLog2e;
     const float r = fmaf(x, kLo, fmaf(x, kLog2e, -t));
     const float e = __builtin_amdgcn_exp2f(t);
