@@ -118,12 +118,26 @@ struct XcaSums {
   }
 };
 
+// 16-bit rows of a job in the wave's slot: two matrices of kSliceRows rows, read back by
+// columns with the LDS transpose loads.  (A product with a 0/1 selection matrix, as the
+// attention kernels transpose, would carry an infinity or NaN of one column into all of
+// its row's: 0 x inf.)
+template <int D>
+constexpr int kXcaStageLd = D + 8;   // 8-byte aligned rows; the writes of 16 rows spread over all banks
+template <int D>
+constexpr int kXcaMat = kSliceRows * kXcaStageLd<D>;
+
+// A wave's slot, in floatx4: its published sums (KT tiles), and the rows it stages.
+template <typename T, int D, int KT>
+constexpr int kXcaSlot = Ty<T>::kNarrow ? (KT * 64 > kXcaMat<D> / 4 ? KT * 64 : kXcaMat<D> / 4)
+                                        : (KT * 64 > kStageWave<D> / 4 ? KT * 64 : kStageWave<D> / 4);
+
 // M[ct][et] += X^T Y over the rows [a, b) of a job (x, y zero outside); SQ: also
 // the diagonal tiles xx += X^T X, yy += Y^T Y (16-bit storage) or the squares by slots.
 template <typename T, int D, bool SQ>
 __device__ __forceinline__ void rows_product(const Raw<T, Geo<D>::KS> (&x)[2], const Raw<T, Geo<D>::KS> (&y)[2],
-                                             int32_t r0, int32_t a, int32_t b, int i, int g, const Sel<T, D>& sel,
-                                             float* stage, floatx4 (&M)[Geo<D>::NT][Geo<D>::NT],
+                                             int32_t r0, int32_t a, int32_t b, int i, int g, float* stage,
+                                             floatx4 (&M)[Geo<D>::NT][Geo<D>::NT],
                                              floatx4 (*xx)[Geo<D>::NT], floatx4 (*yy)[Geo<D>::NT]) {
   constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
   if constexpr (!Ty<T>::kNarrow) {
@@ -140,33 +154,39 @@ __device__ __forceinline__ void rows_product(const Raw<T, Geo<D>::KS> (&x)[2], c
     }
     wave_lds_sync();
     stage_product<D>(stage, stage + kStageMat<D>, r0, a, b, i, g, M);
-    wave_lds_sync();   // the tile may be written again
   } else {
-    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-    auto rows_of = [&](const Raw<T, KS>(&u)[2], int t) -> Raw<T, 8> {
-      return pack_rows<T>(Frag<T, KS>::mma(u[0], sel.m[t], zero), Frag<T, KS>::mma(u[1], sel.m[t], zero));
-    };
+    unsigned short* const sx = reinterpret_cast<unsigned short*>(stage);
+    unsigned short* const sy = sx + kXcaMat<D>;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int at = (16 * s + i) * kXcaStageLd<D> + 16 * t + 4 * g;
+        *reinterpret_cast<u16x4*>(sx + at) = u16x4{x[s][4 * t], x[s][4 * t + 1], x[s][4 * t + 2], x[s][4 * t + 3]};
+        *reinterpret_cast<u16x4*>(sy + at) = u16x4{y[s][4 * t], y[s][4 * t + 1], y[s][4 * t + 2], y[s][4 * t + 3]};
+      }
+    wave_lds_sync();
     Raw<T, 8> py[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      py[t] = rows_of(y, t);
+      py[t] = lds_cols<T>(sy, kXcaStageLd<D>, 16 * t, i, g);
       if constexpr (SQ) (*yy)[t] = Frag<T, 8>::mma(py[t], py[t], (*yy)[t]);
     }
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) {
-      const Raw<T, 8> px = rows_of(x, ct);
+      const Raw<T, 8> px = lds_cols<T>(sx, kXcaStageLd<D>, 16 * ct, i, g);
       if constexpr (SQ) (*xx)[ct] = Frag<T, 8>::mma(px, px, (*xx)[ct]);
 #pragma unroll
       for (int et = 0; et < NT; ++et) M[ct][et] = Frag<T, 8>::mma(px, py[et], M[ct][et]);
     }
   }
+  wave_lds_sync();   // the tile may be written again
 }
 
 // Rows [a, b) of one job into the sums.  Matrices K, V, Q (and dout).
 template <typename T, int D, int NM>
 __device__ __forceinline__ void xca_sums_seg(const Slice<T, Geo<D>::KS, NM>& sb, int32_t r0, int32_t a, int32_t b,
-                                             int i, int g, const Sel<T, D>& sel, float* stage,
-                                             XcaSums<D, NM == 4>& su) {
+                                             int i, int g, float* stage, XcaSums<D, NM == 4>& su) {
   constexpr int KS = Geo<D>::KS;
   using F = Frag<T, KS>;
   Raw<T, KS> x[2], y[2];
@@ -180,10 +200,10 @@ __device__ __forceinline__ void xca_sums_seg(const Slice<T, Geo<D>::KS, NM>& sb,
     }
   };
   rows(0, 2);
-  rows_product<T, D, true>(x, y, r0, a, b, i, g, sel, stage, su.M, &su.k2, &su.q2);
+  rows_product<T, D, true>(x, y, r0, a, b, i, g, stage, su.M, &su.k2, &su.q2);
   if constexpr (NM == 4) {
     rows(1, 3);
-    rows_product<T, D, false>(x, y, r0, a, b, i, g, sel, stage, su.P, nullptr, nullptr);
+    rows_product<T, D, false>(x, y, r0, a, b, i, g, stage, su.P, nullptr, nullptr);
   }
 }
 
@@ -330,8 +350,7 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
                const T* __restrict__ v, T* __restrict__ o) {
   constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
   constexpr int KT = XcaSums<D, false>::kTiles;
-  // a wave's slot: published sums; in fp32 also its staging tile, and the norms
-  constexpr int SL = KT * 64 > kStageWave<D> / 4 ? KT * 64 : kStageWave<D> / 4;
+  constexpr int SL = kXcaSlot<T, D, KT>;
   constexpr bool kHold = Ty<T>::kNarrow || D == 16;
   using F = Frag<T, KS>;
   __shared__ floatx4 s_part[kWaves * SL];
@@ -346,7 +365,6 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
   const int i = lane & 15, g = lane >> 4;
   const size_t rs = (size_t)a.H * D;
   const int32_t n = a.n, G = gridDim.x;
-  const Sel<T, D> sel(i, g);
   floatx4* const slot = s_part + wv * SL;
   float* const stage = reinterpret_cast<float*>(slot);
   float* const norms = s_norm[wv];
@@ -409,7 +427,7 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
 #pragma unroll
         for (int jj = 0; jj < kBlockJobs; ++jj) {
           const int32_t r0 = base + kSliceRows * jj;
-          if (job_overlaps(r0, wa, wb)) xca_sums_seg<T, D, 3>(bk.j[jj], r0, wa, wb, i, g, sel, stage, su);
+          if (job_overlaps(r0, wa, wb)) xca_sums_seg<T, D, 3>(bk.j[jj], r0, wa, wb, i, g, stage, su);
         }
       }
       if (wi.shared) {
@@ -543,7 +561,7 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
                T* __restrict__ dv, float* __restrict__ part) {
   constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
   constexpr int KT = XcaSums<D, true>::kTiles;
-  constexpr int SL = KT * 64 > kStageWave<D> / 4 ? KT * 64 : kStageWave<D> / 4;
+  constexpr int SL = kXcaSlot<T, D, KT>;
   constexpr bool NW = Ty<T>::kNarrow;
   // fp32 at d = 32: rows held through a window's three passes leave one wave per
   // SIMD (or 230 spilled registers); read again for each pass, two
@@ -561,7 +579,6 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
   const int i = lane & 15, g = lane >> 4;
   const size_t rs = (size_t)a.H * D;
   const int32_t n = a.n, G = gridDim.x;
-  const Sel<T, D> sel(i, g);
   floatx4* const slot = s_part + wv * SL;
   float* const stage = reinterpret_cast<float*>(slot);
   float* const norms = s_norm[wv];
@@ -634,7 +651,7 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
 #pragma unroll
           for (int jj = 0; jj < kBlockJobs; ++jj) {
             const int32_t r0 = base + kSliceRows * jj;
-            if (job_overlaps(r0, wa, wb)) xca_sums_seg<T, D, 4>(bk.j[jj], r0, wa, wb, i, g, sel, stage, su);
+            if (job_overlaps(r0, wa, wb)) xca_sums_seg<T, D, 4>(bk.j[jj], r0, wa, wb, i, g, stage, su);
           }
         }
         if (wi.shared) {

@@ -42,9 +42,8 @@ def _bits(dtype, x):
     return workloads.cast_values(np.float32(x).reshape(1), dtype)[0]
 
 
-@pytest.mark.parametrize("name,dtype,thin", [("k", "f32", False), ("k", "f32", True), ("k", "f16", False),
-                                             ("k", "bf16", False), ("q", "f32", False), ("q", "f32", True),
-                                             ("dout", "f32", False), ("dout", "f32", True)])
+@pytest.mark.parametrize("dtype,thin", [("f32", False), ("f32", True), ("f16", False), ("bf16", False)])
+@pytest.mark.parametrize("name", ["q", "k", "dout"])
 @pytest.mark.parametrize("value", ["nan", "inf"])
 @pytest.mark.parametrize("H,d", [(5, 32), (6, 16)])
 def test_not_finite(sla, name, value, H, d, dtype, thin):  # noqa: F811
