@@ -4,6 +4,7 @@
 // host helpers that size and describe a launch.  The design notes are at the
 // top of sla_attn.hip.
 #pragma once
+#include "sla_cache.h"
 #include "sla_common.h"
 
 
@@ -1293,28 +1294,19 @@ struct WinIter {
 // for every item the plan can hold (long windows have more than kMinChunkRows
 // rows), a multiple of 8.
 inline int resident_workgroups(const void* kernel) {
-  struct Entry {
-    const void* kernel;
-    int dev, cap;
-  };
-  static Entry cache[128] = {};
+  static LaunchTable<128> table;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-  for (const Entry& e : cache)
-    if (e.kernel == kernel && e.dev == dev) return e.cap;
-  int per_cu = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * kWaves, 0) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      per_cu < 1 || cus < 1) {
-    per_cu = 2;
-    cus = 256;
-  }
-  for (Entry& e : cache)
-    if (e.kernel == nullptr) {
-      e = Entry{kernel, dev, per_cu * cus};
-      break;
+  return table.get(kernel, dev, [&] {
+    int per_cu = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * kWaves, 0) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        per_cu < 1 || cus < 1) {
+      per_cu = 2;
+      cus = 256;
     }
-  return per_cu * cus;
+    return per_cu * cus;
+  });
 }
 
 // Workgroups of a launch: a whole number k of the device's resident capacity for

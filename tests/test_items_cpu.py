@@ -1,7 +1,11 @@
-"""The schedule's integer arithmetic (csrc/sla_items.h), compiled for the host: every
-wave of every item gets a head of the tensor, also where it is idle (kernels index
-per-head arrays with it), and every share of a long window and every part of a chunk
-is some wave's exactly once."""
+"""Host-checkable headers of the kernels, compiled with g++.
+
+The schedule's integer arithmetic (csrc/sla_items.h): every wave of every item gets a
+head of the tensor, also where it is idle (kernels index per-head arrays with it), and
+every share of a long window and every part of a chunk is some wave's exactly once.
+
+The table of launch figures (csrc/sla_cache.h) under the thread sanitizer: threads
+that look up the same and different kernels for the first time."""
 from __future__ import annotations
 
 import subprocess
@@ -43,21 +47,51 @@ int main() {
 }
 """
 
+TABLE = r"""
+#include "sla_cache.h"
+#include <cstdio>
+#include <thread>
+#include <vector>
+int main() {
+  static sla::LaunchTable<32> table;   // smaller than the keys below: the rest is computed each time
+  static char kernels[24];
+  std::vector<std::thread> threads;
+  std::atomic<int> wrong{0};
+  for (int t = 0; t < 8; ++t)
+    threads.emplace_back([&, t] {
+      for (int round = 0; round < 200; ++round)
+        for (int k = 0; k < 24; ++k)
+          for (int dev = 0; dev < 2; ++dev) {
+            const int key = (k + 3 * t) % 24, want = 256 * (key + 1) + dev;
+            if (table.get(&kernels[key], dev, [&] { return want; }) != want) ++wrong;
+          }
+    });
+  for (auto& th : threads) th.join();
+  return wrong.load() ? 1 : 0;
+}
+"""
+
 
 @pytest.fixture(scope="module")
 def gxx(tmp_path_factory):
     """Compile a harness against the kernels' host-checkable headers and run it."""
-    def run(source, *flags):
+    def run(source, *flags, wrap=()):
         out = tmp_path_factory.mktemp("items")
         (out / "harness.cc").write_text(source)
         exe = str(out / "harness")
         subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-D__host__=", "-D__device__=",
                         "-D__forceinline__=inline", "-I", CSRC, *flags, str(out / "harness.cc"), "-o", exe],
                        check=True, capture_output=True, text=True)
-        return subprocess.run([exe], capture_output=True, text=True, timeout=120)
+        return subprocess.run([*wrap, exe], capture_output=True, text=True, timeout=120)
     return run
 
 
 def test_every_wave_has_a_head_and_every_share_a_wave(gxx):
     res = gxx(HARNESS)
     assert res.returncode == 0, (res.returncode, res.stdout)
+
+
+def test_launch_table_is_safe_with_threads(gxx):
+    # (address randomisation off: the sanitizer's shadow needs the low mappings free)
+    res = gxx(TABLE, "-g", "-pthread", "-fsanitize=thread", wrap=["setarch", "-R"])
+    assert res.returncode == 0, (res.returncode, res.stdout, res.stderr[-2000:])
