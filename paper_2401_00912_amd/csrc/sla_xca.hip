@@ -25,7 +25,7 @@
 // us against 26.9, backward 56.5 against 85.9 on inputs used before; with ten sets in
 // turn, all from HBM, 29.1 against 28.4 and 67.6 against 87.6.  Forward + backward by
 // events 79.9 against 105 us, 151 against 328 on 100k rows in log-normal windows
-// (bf16), 73 against 140 at H = 8, d = 16 (which ran on the vector units).
+// (bf16).
 #include "sla.h"
 #include "sla_attn_core.h"
 
@@ -55,9 +55,27 @@ constexpr float kXcaFloor = 1e-12f;   // least column norm
 // with parts that fill the grid once, 3k rows 51 against 54.
 constexpr int kXcaPartFill = 400;
 
-// 16-bit operands of A in bf16 carry the rounding residual as a second operand
-template <typename T>
-constexpr bool kXcaPair = std::is_same<T, bf16_t>::value;
+// Operands of the d x d matrices (A, B_q, B_k) in the products with rows: 16-bit
+// storage at d = 32 rounds them to the storage type, A in bf16 with its rounding residual
+// as a second operand, B_q and B_k always; at d = 16, as in fp32 storage, they stay fp32
+// and the rows are widened for 16x16x4 products.  60k rows, H = 8, fp16, inputs
+// from HBM: forward 30.7 us (29.6 with A in fp16), backward 59.3 (57.5); with a workgroup
+// per (window, head) on the vector units, also in fp32, 49.9 and 110.
+template <typename T, int D>
+using XcaOp = std::conditional_t<Ty<T>::kNarrow && D == 32, T, float>;
+template <typename O>
+constexpr bool kXcaPair = std::is_same<O, bf16_t>::value;
+
+template <typename T, typename O, int KS>
+__device__ __forceinline__ Raw<O, KS> xca_row(Raw<T, KS> x) {
+  if constexpr (std::is_same<T, O>::value) {
+    return x;
+  } else {
+    float f[KS];
+    Frag<T, KS>::to_f32(x, f);
+    return Frag<O, KS>::from_f32(f);
+  }
+}
 
 // Sums over a window's rows: M[ct][et] = sum k_r[c] q_r[e] (forward and backward),
 // P[ct][et] = sum v_r[c] dout_r[e] (backward), and the squared columns of q and k:
@@ -320,7 +338,7 @@ __device__ __forceinline__ void xca_softmax(floatx4 (&M)[Geo<D>::NT][Geo<D>::NT]
   }
 }
 
-// Operand of a product over c from transposed tiles: lane (i, g) of tile et holds
+// Operand (type T) of a product over c from transposed tiles: lane (i, g) of tile et holds
 // (row e = 16 et + i) the slots c = E(g, r), times mul; `lo` gets the residuals.
 template <typename T, int D, bool LO>
 __device__ __forceinline__ void xca_operand(const floatx4 (&M)[Geo<D>::NT][Geo<D>::NT], float mul,
@@ -353,6 +371,7 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
   constexpr int SL = kXcaSlot<T, D, KT>;
   constexpr bool kHold = Ty<T>::kNarrow || D == 16;
   using F = Frag<T, KS>;
+  using O = XcaOp<T, D>;
   __shared__ floatx4 s_part[kWaves * SL];
   __shared__ WaveMeta s_meta[kWaves];
   __shared__ __align__(16) float s_norm[kWaves][kXcaNorm<D>];
@@ -439,8 +458,8 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
       if (!kHold) refetch(ww.ra, kV);   // in flight under the softmax
       xca_norms<T, D>(su, norms, lane, i, g);
       xca_softmax<T, D, false>(su.M, norms, th, i, g, nullptr);
-      Raw<T, KS> op[NT], opl[NT];
-      xca_operand<T, D, kXcaPair<T>>(su.M, 1.f, op, opl);
+      Raw<O, KS> op[NT], opl[NT];
+      xca_operand<O, D, kXcaPair<O>>(su.M, 1.f, op, opl);
       for (int32_t base = ww.ra; base < ww.rb; base += kBlockRows) {
         if (!(resident && kHold) && (base != ww.ra || kHold)) refetch(base, kV);
 #pragma unroll
@@ -450,12 +469,13 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
             const int32_t r0 = base + kSliceRows * jj;
             if (!sub_overlaps(r0, s, wa, wb)) continue;
             const int32_t row = r0 + 16 * s + i;
+            const Raw<O, KS> vr = xca_row<T, O, KS>(bk.j[jj].x[1][s]);
             float x[KS];
 #pragma unroll
             for (int et = 0; et < NT; ++et) {
               const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-              floatx4 d4 = F::mma(op[et], bk.j[jj].x[1][s], zero);
-              if constexpr (kXcaPair<T>) d4 = F::mma(opl[et], bk.j[jj].x[1][s], d4);
+              floatx4 d4 = Frag<O, KS>::mma(op[et], vr, zero);
+              if constexpr (kXcaPair<O>) d4 = Frag<O, KS>::mma(opl[et], vr, d4);
 #pragma unroll
               for (int j = 0; j < 4; ++j) x[4 * et + j] = d4[j];
             }
@@ -491,7 +511,7 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
 // and dkh are formed again from registers rather than held (matrix products are
 // cheap here, registers are not).
 //
-// 16-bit storage: B_q[e][c] = tau dG[e][c] / nk_c spans the range of 1 / nk, and a
+// 16-bit storage at d = 32: B_q[e][c] = tau dG[e][c] / nk_c spans the range of 1 / nk, and a
 // floored norm (a zero column) makes that 1e12 times wider than the rest.  So the
 // column factor is split: B_q[e][c] k[r][c] = (tau dG[e][c] s_c / nk_c)(k[r][c] /
 // s_c) with s_c = 2^floor(log2 nk_c).  The first factor, within [1/2, 1] of tau dG,
@@ -511,11 +531,11 @@ __device__ __forceinline__ float xca_pow2_floor(float x) {
   return __uint_as_float(__float_as_uint(x) & 0x7f800000u);
 }
 
-// A row's slots times powers of two (exact); fp32 rows stay as they are.
-template <typename T, int KS>
-__device__ __forceinline__ Raw<T, KS> xca_rescale(Raw<T, KS> x, const float (&nrm)[KS]) {
-  if constexpr (!Ty<T>::kNarrow) return x;
-  Raw<T, KS> r;
+// A row's slots times powers of two (exact); rows against fp32 operands stay as they are.
+template <typename T, typename O, int KS>
+__device__ __forceinline__ Raw<O, KS> xca_rescale(Raw<T, KS> x, const float (&nrm)[KS]) {
+  if constexpr (!Ty<O>::kNarrow) return xca_row<T, O, KS>(x);
+  Raw<O, KS> r;
 #pragma unroll
   for (int j = 0; j < KS; ++j) {
     // 1 / 2^e from the exponent bits: norms are normal numbers below 2^126
@@ -527,21 +547,22 @@ __device__ __forceinline__ Raw<T, KS> xca_rescale(Raw<T, KS> x, const float (&nr
 
 template <typename T, int D>
 struct XcaBwdOp {
+  using O = XcaOp<T, D>;
   static constexpr int NT = Geo<D>::NT, KS = Geo<D>::KS;
-  static constexpr int NL = Ty<T>::kNarrow ? NT : 1;
-  Raw<T, KS> bq[NT], bql[NL];   // scaled B_q: row e = 16 t + i, slots c (and residual)
-  Raw<T, KS> bk[NT], bkl[NL];   // scaled B_k^T: row c = 16 t + i, slots e
+  static constexpr int NL = Ty<O>::kNarrow ? NT : 1;
+  Raw<O, KS> bq[NT], bql[NL];   // scaled B_q: row e = 16 t + i, slots c (and residual)
+  Raw<O, KS> bk[NT], bkl[NL];   // scaled B_k^T: row c = 16 t + i, slots e
   float iq, ik;                 // the scales' inverses
   // dqh and dkh of a row by slots
   __device__ __forceinline__ void grads(const Raw<T, KS>& qr, const Raw<T, KS>& kr, const float (&nq)[KS],
                                         const float (&nk)[KS], float (&gq)[KS], float (&gk)[KS]) const {
-    using F = Frag<T, KS>;
+    using F = Frag<O, KS>;
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-    const Raw<T, KS> kb = xca_rescale<T, KS>(kr, nk), qb = xca_rescale<T, KS>(qr, nq);
+    const Raw<O, KS> kb = xca_rescale<T, O, KS>(kr, nk), qb = xca_rescale<T, O, KS>(qr, nq);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       floatx4 x = F::mma(bq[t], kb, zero), y = F::mma(bk[t], qb, zero);
-      if constexpr (Ty<T>::kNarrow) {
+      if constexpr (Ty<O>::kNarrow) {
         x = F::mma(bql[t], kb, x);
         y = F::mma(bkl[t], qb, y);
       }
@@ -567,6 +588,8 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
   // SIMD (or 230 spilled registers); read again for each pass, two
   constexpr bool kHold = NW || D == 16;
   using F = Frag<T, KS>;
+  using O = XcaOp<T, D>;
+  constexpr bool NO = Ty<O>::kNarrow;
   __shared__ floatx4 s_part[kWaves * SL];
   __shared__ WaveMeta s_meta[kWaves];
   __shared__ __align__(16) float s_norm[kWaves][kXcaNorm<D>];
@@ -641,7 +664,7 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
         xca_slots<D>(norms + 3 * D, g, rk);
       };
       XcaBwdOp<T, D> op;
-      Raw<T, KS> at[NT], atl[NT];   // A^T: row c = 16 t + i, slots e
+      Raw<O, KS> at[NT], atl[NT];   // A^T: row c = 16 t + i, slots e
       {
         // pass 1: G, the norms, dA
         XcaSums<D, true> su;
@@ -668,7 +691,7 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
         for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
           for (int et = 0; et < NT; ++et) tr.M[ct][et] = su.M[ct][et];
-        transposed_operand<T, D, kXcaPair<T>>(tr, 1.f, stage, i, g, at, atl);
+        transposed_operand<O, D, kXcaPair<O>>(tr, 1.f, stage, i, g, at, atl);
         // dG (in P), the temperature share, B_q (in M) and B_k (in P)
         float pt = 0.f, mq = 0.f, mk = 0.f;
         float fk[KS];
@@ -677,7 +700,7 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
           xca_slots<D>(norms + D, g, nk);
           xca_slots<D>(norms + 3 * D, g, fk);
 #pragma unroll
-          for (int r = 0; r < KS; ++r) fk[r] *= th * (NW ? xca_pow2_floor(nk[r]) : 1.f);
+          for (int r = 0; r < KS; ++r) fk[r] *= th * (NO ? xca_pow2_floor(nk[r]) : 1.f);
         }
 #pragma unroll
         for (int et = 0; et < NT; ++et) {
@@ -687,7 +710,7 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
 #pragma unroll
             for (int j = 0; j < 4; ++j) rsum += su.M[ct][et][j] * su.P[ct][et][j];
           rsum = sum_groups(rsum);
-          const float fq = th * norms[2 * D + 16 * et + i] * (NW ? xca_pow2_floor(norms[16 * et + i]) : 1.f);
+          const float fq = th * norms[2 * D + 16 * et + i] * (NO ? xca_pow2_floor(norms[16 * et + i]) : 1.f);
 #pragma unroll
           for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
@@ -704,12 +727,12 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
         // waves that share a window hold the same sum; the first of them writes it
         if (lane == 0 && ww.rb > ww.ra && (!wi.shared || (ww.pair ? (wv & 1) : wv) == 0))
           part[(size_t)wi.window(ww) * a.H + ww.h] = pt;
-        const float sq = NW ? pow2_scale_to_one(wave_reduce<true>(mq)) : 1.f;
-        const float sk = NW ? pow2_scale_to_one(wave_reduce<true>(mk)) : 1.f;
+        const float sq = NO ? pow2_scale_to_one(wave_reduce<true>(mq)) : 1.f;
+        const float sk = NO ? pow2_scale_to_one(wave_reduce<true>(mk)) : 1.f;
         op.iq = 1.f / sq;
         op.ik = 1.f / sk;
-        xca_operand<T, D, NW>(su.M, sq, op.bq, op.bql);
-        transposed_operand<T, D, NW>(tr, sk, stage, i, g, op.bk, op.bkl);
+        xca_operand<O, D, NO>(su.M, sq, op.bq, op.bql);
+        transposed_operand<O, D, NO>(tr, sk, stage, i, g, op.bk, op.bkl);
       }
       // pass 2: dv, and the projections s_e, t_c by slots
       float ps[KS], pk[KS];
@@ -727,12 +750,13 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
             const auto& sb = bk.j[jj];
             const bool in = sb.ok[s] && row >= wa && row < wb;
             __builtin_amdgcn_sched_barrier(0);   // one sub-tile's operands live at a time
+            const Raw<O, KS> dr = xca_row<T, O, KS>(sb.x[3][s]);
             float x[KS];
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
               const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-              floatx4 d4 = F::mma(at[t], sb.x[3][s], zero);
-              if constexpr (kXcaPair<T>) d4 = F::mma(atl[t], sb.x[3][s], d4);
+              floatx4 d4 = Frag<O, KS>::mma(at[t], dr, zero);
+              if constexpr (kXcaPair<O>) d4 = Frag<O, KS>::mma(atl[t], dr, d4);
 #pragma unroll
               for (int j = 0; j < 4; ++j) x[4 * t + j] = d4[j];
             }

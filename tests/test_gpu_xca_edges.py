@@ -59,3 +59,52 @@ def test_not_finite(sla, name, value, H, d, dtype, thin):  # noqa: F811
         fine = np.isfinite(r)
         tol = TOL[dtype] if label == "o" else GRAD_TOL[dtype]
         assert np.abs(x[fine] - r[fine]).max() <= tol * np.abs(r[fine]).max(), label
+
+
+def _with_magnitudes(q, k, v, do, tau):
+    """One window and head in float64: (o, dv, dqh / nq) and, beside each, the sum of the
+    magnitudes of the terms it is made of."""
+    nq, nk = (np.maximum(np.sqrt((x * x).sum(0)), 1e-12) for x in (q, k))
+    g = tau * ((q / nq).T @ (k / nk))
+    a = np.exp(g - g.max(1, keepdims=True))
+    a /= a.sum(1, keepdims=True)
+    da, da_mag = do.T @ v, np.abs(do).T @ np.abs(v)
+    dg = a * (da - (a * da).sum(1, keepdims=True))
+    dg_mag = a * (da_mag + (a * da_mag).sum(1, keepdims=True))
+    b, b_mag = tau * dg / nk / nq[:, None], abs(tau) * dg_mag / nk / nq[:, None]
+    return ((v @ a.T, np.abs(v) @ a.T), (do @ a, np.abs(do) @ a), (k @ b.T, np.abs(k) @ b_mag.T))
+
+
+@pytest.mark.parametrize("dtype,half_ulp", [("f16", 2.0 ** -11), ("bf16", 2.0 ** -8)])
+def test_narrow_heads_in_fp32(sla, dtype, half_ulp):  # noqa: F811
+    # at d = 16 the weights A and the matrices of the gradients are fp32: where terms
+    # cancel, or a row is far smaller than its column's norm, an output is off by its own
+    # rounding and what fp32 leaves, and not by a rounding of A, B or the row to 16 bits
+    rng = np.random.default_rng([92, len(dtype)])
+    lengths, H, d = rng.integers(4, 9, size=60).astype(np.int64), 6, 16
+    ids = workloads.ids_from_lengths(lengths, rng)
+    f32 = [rng.standard_normal((ids.size, H, d)).astype(np.float32) for _ in range(4)]
+    f32[3] *= 1e3   # (dq of the rows below stays above fp16's subnormals)
+    zero = np.zeros(ids.size, dtype=bool)
+    for w in range(lengths.size):
+        rows = np.flatnonzero(ids == w)
+        f32[1][rows[0]] *= 1e3     # the norm of every k column
+        f32[1][rows[1:]] *= 1e-3   # and rows far below it,
+        f32[0][rows[1::2]] = 0     # whose dq, where q is zero, is dqh / nq alone
+        zero[rows[1::2]] = True
+    t = [workloads.cast_values(x, dtype) for x in f32]
+    tau = np.linspace(-1.0, 3.0, H).astype(np.float32)
+    got, _ = run_xca(sla, ids, lengths.size, t, tau, dtype)
+    q, k, v, do = (oracle.widen(x, dtype) for x in t)
+    for w in range(lengths.size):
+        rows = ids == w
+        for h in range(H):
+            o, dv, dq = _with_magnitudes(*(x[rows, h] for x in (q, k, v, do)), float(tau[h]))
+            for label, x, (r, mag), which in (("o", got[0], o, rows[rows]), ("dv", got[3], dv, rows[rows]),
+                                              ("dq", got[1], dq, zero[rows])):
+                # sums over at most 8 rows, 16 columns and their use in a logit up to 3,
+                # an exponential, divisions: 128 roundings of 2^-24 at most; the storage
+                # type's subnormals
+                tol = half_ulp * np.abs(r) + 128 * 2.0 ** -24 * mag + 2.0 ** -25
+                bad = np.abs(x[rows, h] - r)[which] > tol[which]
+                assert not bad.any(), (label, w, h, int(bad.sum()))
