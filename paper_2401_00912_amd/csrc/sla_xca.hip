@@ -77,6 +77,27 @@ __device__ __forceinline__ Raw<O, KS> xca_row(Raw<T, KS> x) {
   }
 }
 
+// A product with a row, over the head dim.  fp32 operands: 16x16x4 products in pairs, added
+// as a tree, so that a sum of 32 terms goes through 10 additions one after the other
+// instead of 32 (fp32 o and dv of a 45k-row frame, d = 32: relative
+// error 1.03e-7 against 1.30e-7 in one chain and 1.06e-7 on the vector units; same time).
+template <typename O, int KS>
+__device__ __forceinline__ floatx4 xca_mma(Raw<O, KS> a, Raw<O, KS> b) {
+  const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (Ty<O>::kNarrow) {
+    return Frag<O, KS>::mma(a, b, zero);
+  } else {
+    floatx4 c[KS / 2];
+#pragma unroll
+    for (int k = 0; k < KS / 2; ++k) {
+      c[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2 * k], b[2 * k], zero, 0, 0, 0);
+      c[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2 * k + 1], b[2 * k + 1], c[k], 0, 0, 0);
+    }
+    if constexpr (KS == 8) return (c[0] + c[1]) + (c[2] + c[3]);
+    else return c[0] + c[1];
+  }
+}
+
 // Sums over a window's rows: M[ct][et] = sum k_r[c] q_r[e] (forward and backward),
 // P[ct][et] = sum v_r[c] dout_r[e] (backward), and the squared columns of q and k:
 // 16-bit storage takes them from the diagonals of the tiles q^T q and k^T k, whose
@@ -473,8 +494,7 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
             float x[KS];
 #pragma unroll
             for (int et = 0; et < NT; ++et) {
-              const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-              floatx4 d4 = Frag<O, KS>::mma(op[et], vr, zero);
+              floatx4 d4 = xca_mma<O, KS>(op[et], vr);
               if constexpr (kXcaPair<O>) d4 = Frag<O, KS>::mma(opl[et], vr, d4);
 #pragma unroll
               for (int j = 0; j < 4; ++j) x[4 * et + j] = d4[j];
@@ -754,8 +774,7 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
             float x[KS];
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-              const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-              floatx4 d4 = Frag<O, KS>::mma(at[t], dr, zero);
+              floatx4 d4 = xca_mma<O, KS>(at[t], dr);
               if constexpr (kXcaPair<O>) d4 = Frag<O, KS>::mma(atl[t], dr, d4);
 #pragma unroll
               for (int j = 0; j < 4; ++j) x[4 * t + j] = d4[j];
