@@ -286,8 +286,10 @@ __device__ __forceinline__ void xca_norms(const XcaSums<D, BWD>& su, float* norm
   }
   wave_lds_sync();
   if (lane < 2 * D) {
+    // a norm whose square has overflowed divides to zero: its reciprocal is zero, and the
+    // norm itself finite, so that the steps of xca_unit leave that zero
     const float x = fmaxf(sqrtf(norms[lane]), kXcaFloor);
-    norms[lane] = x;
+    norms[lane] = fminf(x, 3.0e38f);
     norms[2 * D + lane] = recip<T>(x);
   }
   wave_lds_sync();
@@ -544,6 +546,12 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
 __device__ __forceinline__ float xca_unit(float x, float y, float ry) {
   const float h = x * ry;
   return fmaf(fmaf(-h, y, x), ry, h);
+}
+
+// The same where the quotient may overflow (a gradient through a floored norm): to infinity.
+__device__ __forceinline__ float xca_div(float x, float y, float ry) {
+  const float h = x * ry;
+  return fabsf(h) < 3.4e38f ? fmaf(fmaf(-h, y, x), ry, h) : h;
 }
 
 // 2^floor(log2 x) for a normal x > 0 (the norms: at least 1e-12)
@@ -852,8 +860,8 @@ void k_xca_bwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
             for (int r = 0; r < KS; ++r) {
               const float xq = gq[r] - xca_unit(qf[r], nq[r], rq[r]) * ps[r];
               const float xk = gk[r] - xca_unit(kf[r], nk[r], rk[r]) * pk[r];
-              gq[r] = NW ? xq * rq[r] : xca_unit(xq, nq[r], rq[r]);
-              gk[r] = NW ? xk * rk[r] : xca_unit(xk, nk[r], rk[r]);
+              gq[r] = NW ? xq * rq[r] : xca_div(xq, nq[r], rq[r]);
+              gk[r] = NW ? xk * rk[r] : xca_div(xk, nk[r], rk[r]);
             }
             RowIO<T, D>::put(dq, row_off(sb.o[s], rs, col), g, F::from_f32(gq), in);
             RowIO<T, D>::put(dk, row_off(sb.o[s], rs, col), g, F::from_f32(gk), in);

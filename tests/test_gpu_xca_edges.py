@@ -124,3 +124,28 @@ def test_fp32_error_on_either_side(sla, H, d):  # noqa: F811
         err[W > 80] = [float(np.linalg.norm(got[m] - ref[m]) / np.linalg.norm(ref[m])) for m in (0, 3)]
     # (errors of 160k values: their ratio scatters by well under a percent)
     assert all(a <= 1.05 * b for a, b in zip(err[False], err[True])), err
+
+
+@pytest.mark.parametrize("dtype,thin", [("f32", False), ("f32", True), ("bf16", False)])
+@pytest.mark.parametrize("d", [16, 32])
+def test_norms_beyond_fp32(sla, d, dtype, thin):  # noqa: F811
+    # a q column whose squares overflow fp32 divides to zero: a uniform softmax row, zero
+    # dq, no NaN anywhere; and a gradient through a floored norm that passes the largest
+    # fp32 value is infinite, of the exact value's sign
+    rng = np.random.default_rng([94, d, len(dtype), thin])
+    H, lengths = 2, THIN if thin else WINDOWS
+    ids = workloads.ids_from_lengths(lengths, rng)
+    f32 = [rng.standard_normal((ids.size, H, d)).astype(np.float32) for _ in range(4)]
+    f32[0][:, 0, 3] = np.float32(1e25) * np.sign(f32[0][:, 0, 3])
+    f32[0][:, 1, 5] = 0
+    f32[2][:, 1], f32[3][:, 1] = f32[2][:, 1] * 1e16, f32[3][:, 1] * 1e16
+    t = [workloads.cast_values(x, dtype) for x in f32]
+    got, ref = run_xca(sla, ids, lengths.size, t, np.array([1.0, 1.0]), dtype)
+    v, live = oracle.widen(t[2], dtype), np.isin(ids, np.flatnonzero(lengths > 1))
+    assert all(np.isfinite(x[:, 0]).all() for x in got[:4])
+    assert (got[1][:, 0, 3] == 0).all()
+    assert np.abs(got[0][:, 0, 3] - v[:, 0].mean(1)).max() <= TOL[dtype] * np.abs(v[:, 0]).max()
+    big = np.abs(ref[1][:, 1, 5]) > 3.5e38
+    assert big[live].mean() > 0.5
+    assert np.array_equal(got[1][big, 1, 5], np.sign(ref[1][big, 1, 5]) * np.inf)
+    assert not np.isnan(got[1][:, 1]).any()
