@@ -375,9 +375,13 @@ sla_status_t sla_forward_scatter(const void* plan, size_t plan_bytes, int64_t n,
  * tau: device float [heads], the per-head temperatures (4-byte aligned).  Same
  * plan, row layouts, dtypes and errors as sla_forward (rows in no window are
  * not written), plus SLA_E_UNSUPPORTED when num_windows x heads x 256 exceeds
- * 2^32 - 1 (one 256-thread workgroup per window and head, windows padded
- * to a multiple of 8).  fp32 arithmetic on
- * the vector units; outputs rounded to `dtype`.  Its backward is sla_backward_xca.
+ * 2^32 - 1 (windows padded to a multiple of 8: some scenes run one 256-thread workgroup
+ * per window and head, the others the attention's work items; which, by num_windows,
+ * heads and n alone).  The sums over rows, the norms and the softmax are fp32; A and the
+ * gradients' d x d matrices are fp32 in the products with rows too, except in 16-bit
+ * storage at head_dim 32, where they are rounded to `dtype` (fp16: A once, the others as a
+ * pair of value and residual; bf16: all as pairs).  Outputs are rounded to `dtype`.  Its
+ * backward is sla_backward_xca.
  */
 sla_status_t sla_forward_xca(const void* plan, size_t plan_bytes, int64_t n, int32_t num_windows,
                              sla_dtype_t dtype, int32_t heads, int32_t head_dim, const float* tau,

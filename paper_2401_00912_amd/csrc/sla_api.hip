@@ -314,8 +314,8 @@ SLA_EXPORT sla_status_t sla_forward_xca(const void* plan, size_t plan_bytes, int
                                         const void* k, const void* v, void* o, sla_stream_t stream) {
   const sla_status_t st = check_tensor_args(n, num_windows, (int)dtype, heads, head_dim, plan, plan_bytes);
   if (st != SLA_OK) return st;
-  // one 256-thread workgroup per (window, head), windows padded to a multiple of
-  // 8: the launch's work-items must fit 32 bits
+  // the kernels with a 256-thread workgroup per (window, head), windows padded to a
+  // multiple of 8: the launch's work-items must fit 32 bits
   if (((int64_t)num_windows + 7) / 8 * 8 * heads * 256 > (int64_t)UINT32_MAX) return SLA_E_UNSUPPORTED;
   if (n == 0) return SLA_OK;
   if (!tau || !q || !k || !v || !o) return SLA_E_ARG;

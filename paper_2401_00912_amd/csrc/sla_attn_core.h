@@ -1294,7 +1294,7 @@ struct WinIter {
 // for every item the plan can hold (long windows have more than kMinChunkRows
 // rows), a multiple of 8.
 inline int resident_workgroups(const void* kernel) {
-  static LaunchTable<128> table;
+  static LaunchTable<256> table;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;
   return table.get(kernel, dev, [&] {

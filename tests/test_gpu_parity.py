@@ -1187,7 +1187,7 @@ def _split_overflow(name, x, r, dtype, label):
     return x, r
 
 
-def xca_backward_parity(S, ids, offsets, n, W, q, k, v, do, tau, dtype, label=""):
+def xca_backward_parity(S, ids, offsets, n, W, q, k, v, do, tau, dtype, label="", dtau_scale=1e-30):
     import torch
 
     plan = build(S, ids=ids, W=W, offsets=offsets, n=n)
@@ -1209,7 +1209,7 @@ def xca_backward_parity(S, ids, offsets, n, W, q, k, v, do, tau, dtype, label=""
         _say(f"[xca-bwd {label}] {name} n={n} dtype={dtype} rel_err={err:.3e}")
         assert err <= GRAD_TOL[dtype], f"{label}: {name} relative error {err:.3e}"
     dt = dtau.cpu().numpy().astype(np.float64)
-    derr = float(np.abs(dt - ref[3]).max()) / max(float(np.abs(ref[3]).max()), 1e-30)
+    derr = float(np.abs(dt - ref[3]).max()) / max(float(np.abs(ref[3]).max()), dtau_scale)
     _say(f"[xca-bwd {label}] dtau rel_err={derr:.3e}")
     assert derr <= XCA_DTAU_TOL, f"{label}: dtau relative error {derr:.3e}"
     return got, dt

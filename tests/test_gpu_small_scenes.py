@@ -8,6 +8,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
+import oracle
 import workloads
 from tests.test_gpu_parity import (_xca_tau, backward_parity, forward_parity, sla, xca_backward_parity,  # noqa: F401
                                    xca_parity)
@@ -36,14 +37,46 @@ def test_parts(sla, scene, dtype, H, d):  # noqa: F811
     label = f"{scene} H{H} d{d}"
     forward_parity(sla, ids, None, n, W, q, k, v, dtype, label=label)
     xca_parity(sla, ids, None, n, W, q, k, v, _xca_tau(H), dtype, label=label)
-    # alone in its window a row has dq = dk = 0: what fp32 leaves is the rounding of
-    # cancelling terms up to max|dout| max|v|, a few 2^-24 of them, which the error
-    # measure's floor (1e-3 of that) turns into a few 6e-5, above the 1e-5 bar
     if scene != "one-row":
         backward_parity(sla, ids, None, n, W, q, k, v, do, dtype, label=label)
-    # (fp32 XCA on windows this thin runs on the vector units, without parts)
-    if scene != "one-row" and dtype != "f32":
-        xca_backward_parity(sla, ids, None, n, W, q, k, v, do, _xca_tau(H), dtype, label=label)
+    else:
+        one_row_backward(sla, ids, W, q, k, v, do, dtype)
+    # (so few pairs of windows and heads run the kernels with a workgroup each, without parts)
+    # dtau sums the shares of windows of a few rows, of either sign: against their magnitudes
+    xca_backward_parity(sla, ids, None, n, W, q, k, v, do, _xca_tau(H), dtype, label=label,
+                        dtau_scale=dtau_magnitude(ids, W, H, *(oracle.widen(x, dtype) for x in (q, k, v, do))))
+
+
+def dtau_magnitude(ids, W, H, q, k, v, do):
+    """The least over the heads of sum |dG N| over windows and entries (tau as in _xca_tau)."""
+    tau, mag = _xca_tau(H), np.zeros(H)
+    for w in range(W):
+        rows = ids == w
+        if rows.any():
+            for h in range(H):
+                qh, kh = (x[rows, h] / np.maximum(np.sqrt((x[rows, h] ** 2).sum(0)), 1e-12) for x in (q, k))
+                nn = qh.T @ kh
+                a = np.exp(tau[h] * nn - (tau[h] * nn).max(1, keepdims=True))
+                a /= a.sum(1, keepdims=True)
+                da = do[rows, h].T @ v[rows, h]
+                mag[h] += np.abs(a * (da - (a * da).sum(1, keepdims=True)) * nn).sum()
+    return mag.min()
+
+
+def one_row_backward(S, ids, W, q, k, v, do, dtype):
+    """Alone in its window a row has dv = dout and dq = dk = 0: what is left is the rounding
+    of two cancelling sums of d terms up to max|dout| max|v| each (phi'(q) phi(k) / (phi(q).
+    phi(k)) <= 1), whose operands are rounded once or twice to the storage type, which the
+    error measure of the others (a relative one) does not fit."""
+    from tests.gpu_util import TOL, to_dev, to_host64
+
+    plan = S.build_segments(to_dev(ids.astype(np.int32)), num_windows=W)
+    got = [to_host64(t, dtype) for t in S.backward(plan, *(to_dev(x, dtype) for x in (q, k, v, do)))]
+    v64, do64 = (oracle.widen(x, dtype) for x in (v, do))
+    unit = {"f32": 2.0 ** -24, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype]
+    left = 4 * unit * q.shape[2] * np.abs(do64).max() * np.abs(v64).max()
+    assert np.abs(got[0]).max() <= left and np.abs(got[1]).max() <= left
+    assert np.abs(got[2] - do64).max() <= TOL[dtype] * np.abs(do64).max()
 
 
 @pytest.mark.parametrize("n,W", [(60000, 2049), (60001, 2049), (160000, 2048), (160001, 2048), (160001, 7), (130000, 2048),

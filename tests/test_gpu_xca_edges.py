@@ -1,7 +1,9 @@
-"""XCA at the edges of its values.  An infinity or NaN in q, k or dout reaches the
-outputs and gradients that the definition carries it to and no others, in every
-storage type and on both sides of the line between the vector-unit and the
-matrix-core kernels (fp32, 28 rows per window slot)."""
+"""XCA at the edges of its values, on each of its three sets of kernels: a workgroup per
+(window, head) with the long-window passes (few pairs), without (more pairs of thin
+windows), and work items (many pairs; about 31 rows a slot, so that chunks are split
+into parts).  An infinity or NaN in q, k or dout reaches the outputs and gradients that
+the definition carries it to and no others; zero columns, norms beyond fp32, one-row
+windows; the precision of each."""
 from __future__ import annotations
 
 import numpy as np
@@ -10,12 +12,18 @@ import pytest
 import oracle
 import workloads
 from tests.gpu_util import TOL, to_dev, to_host64
-from tests.test_gpu_parity import GRAD_TOL, sla  # noqa: F401
+from tests.test_gpu_parity import GRAD_TOL, sla, xca_backward_parity, xca_parity  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-WINDOWS = np.array([40, 64, 33, 300, 28, 50, 90], dtype=np.int64)   # 86 rows per slot: the matrix-core kernels
-THIN = np.concatenate([WINDOWS, np.ones(40, dtype=np.int64)])        # 13 per slot: fp32 on the vector units
+# the windows looked at, and what stands beside them: with 6 heads 42, 1,980 and 1,980
+# pairs, at 86, 4 and 31 rows per slot
+WINDOWS = np.array([40, 64, 33, 300, 28, 50, 90], dtype=np.int64)
+BESIDE = {"long": np.zeros(0, dtype=np.int64), "plain": np.arange(323) % 4, "items": 26 + np.arange(323) % 10}
+
+
+def scene(layout, windows=WINDOWS):
+    return np.concatenate([windows, BESIDE[layout]]).astype(np.int64)
 
 
 def run_xca(S, ids, W, tensors, tau, dtype):
@@ -42,13 +50,13 @@ def _bits(dtype, x):
     return workloads.cast_values(np.float32(x).reshape(1), dtype)[0]
 
 
-@pytest.mark.parametrize("dtype,thin", [("f32", False), ("f32", True), ("f16", False), ("bf16", False)])
+@pytest.mark.parametrize("layout,value", [("long", "nan"), ("long", "inf"), ("plain", "nan"), ("items", "nan")])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("name", ["q", "k", "dout"])
-@pytest.mark.parametrize("value", ["nan", "inf"])
-@pytest.mark.parametrize("H,d", [(5, 32), (6, 16)])
-def test_not_finite(sla, name, value, H, d, dtype, thin):  # noqa: F811
-    rng = np.random.default_rng([91, H, d, len(dtype), thin])
-    lengths = THIN if thin else WINDOWS
+@pytest.mark.parametrize("H,d", [(6, 32), (6, 16)])
+def test_not_finite(sla, name, value, H, d, dtype, layout):  # noqa: F811
+    rng = np.random.default_rng([91, H, d, len(dtype), len(layout)])
+    lengths = scene(layout)
     ids = workloads.ids_from_lengths(lengths, rng)
     t = dict(zip(("q", "k", "v", "dout"), (workloads.normal_values(rng, ids.size, H, d, dtype) for _ in range(4))))
     for w, h, e in ((2, 1, d - 1), (3, 0, 4)):   # a window of one chunk, and a long one
@@ -76,12 +84,13 @@ def _with_magnitudes(q, k, v, do, tau):
 
 
 @pytest.mark.parametrize("dtype,half_ulp", [("f16", 2.0 ** -11), ("bf16", 2.0 ** -8)])
-def test_narrow_heads_in_fp32(sla, dtype, half_ulp):  # noqa: F811
+@pytest.mark.parametrize("windows", [60, 640])   # the kernels of few pairs, and work items
+def test_narrow_heads_in_fp32(sla, dtype, half_ulp, windows):  # noqa: F811
     # at d = 16 the weights A and the matrices of the gradients are fp32: where terms
     # cancel, or a row is far smaller than its column's norm, an output is off by its own
     # rounding and what fp32 leaves, and not by a rounding of A, B or the row to 16 bits
     rng = np.random.default_rng([92, len(dtype)])
-    lengths, H, d = rng.integers(4, 9, size=60).astype(np.int64), 6, 16
+    lengths, H, d = rng.integers(4, 9, size=windows).astype(np.int64), 6, 16
     ids = workloads.ids_from_lengths(lengths, rng)
     f32 = [rng.standard_normal((ids.size, H, d)).astype(np.float32) for _ in range(4)]
     f32[3] *= 1e3   # (dq of the rows below stays above fp16's subnormals)
@@ -115,32 +124,33 @@ def test_fp32_error_on_either_side(sla, H, d):  # noqa: F811
     # the same windows with and without empty slots beside them: on the vector units and on
     # the matrix cores; neither o nor dv is further from float64 there
     rng = np.random.default_rng([93, H, d])
-    lengths = rng.integers(10, 120, size=80).astype(np.int64)
+    lengths = rng.integers(10, 120, size=400).astype(np.int64)
     ids = workloads.ids_from_lengths(lengths, rng)
     t = [workloads.normal_values(rng, ids.size, H, d, "f32") for _ in range(4)]
     err = {}
-    for W in (80, 80 + ids.size // 28):
+    for W in (400, 400 + ids.size // 28):
         got, ref = run_xca(sla, ids, W, t, np.linspace(0.5, 3.0, H), "f32")
-        err[W > 80] = [float(np.linalg.norm(got[m] - ref[m]) / np.linalg.norm(ref[m])) for m in (0, 3)]
-    # (errors of 160k values: their ratio scatters by well under a percent)
+        err[W > 400] = [float(np.linalg.norm(got[m] - ref[m]) / np.linalg.norm(ref[m])) for m in (0, 3)]
+    # (errors of 3 million values: their ratio scatters by well under a percent)
     assert all(a <= 1.05 * b for a, b in zip(err[False], err[True])), err
 
 
-@pytest.mark.parametrize("dtype,thin", [("f32", False), ("f32", True), ("bf16", False)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("layout", sorted(BESIDE))
 @pytest.mark.parametrize("d", [16, 32])
-def test_norms_beyond_fp32(sla, d, dtype, thin):  # noqa: F811
+def test_norms_beyond_fp32(sla, d, layout, dtype):  # noqa: F811
     # a q column whose squares overflow fp32 divides to zero: a uniform softmax row, zero
     # dq, no NaN anywhere; and a gradient through a floored norm that passes the largest
     # fp32 value is infinite, of the exact value's sign
-    rng = np.random.default_rng([94, d, len(dtype), thin])
-    H, lengths = 2, THIN if thin else WINDOWS
+    rng = np.random.default_rng([94, d, len(dtype), len(layout)])
+    H, lengths = 6, scene(layout)
     ids = workloads.ids_from_lengths(lengths, rng)
     f32 = [rng.standard_normal((ids.size, H, d)).astype(np.float32) for _ in range(4)]
     f32[0][:, 0, 3] = np.float32(1e25) * np.sign(f32[0][:, 0, 3])
     f32[0][:, 1, 5] = 0
     f32[2][:, 1], f32[3][:, 1] = f32[2][:, 1] * 1e16, f32[3][:, 1] * 1e16
     t = [workloads.cast_values(x, dtype) for x in f32]
-    got, ref = run_xca(sla, ids, lengths.size, t, np.array([1.0, 1.0]), dtype)
+    got, ref = run_xca(sla, ids, lengths.size, t, np.ones(H), dtype)
     v, live = oracle.widen(t[2], dtype), np.isin(ids, np.flatnonzero(lengths > 1))
     assert all(np.isfinite(x[:, 0]).all() for x in got[:4])
     assert (got[1][:, 0, 3] == 0).all()
@@ -149,3 +159,47 @@ def test_norms_beyond_fp32(sla, d, dtype, thin):  # noqa: F811
     assert big[live].mean() > 0.5
     assert np.array_equal(got[1][big, 1, 5], np.sign(ref[1][big, 1, 5]) * np.inf)
     assert not np.isnan(got[1][:, 1]).any()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("layout", ["plain", "items"])
+@pytest.mark.parametrize("d", [16, 32])
+def test_degenerate(sla, d, layout, dtype):  # noqa: F811
+    # a zero q column and a zero k column (their norms take the floor), tau = 0, a sharp
+    # softmax, one- and two-row windows with small columns (whose dq and dk are 0 for one
+    # row): as the tests of few windows, on the kernels of more
+    rng = np.random.default_rng([95, d, len(dtype), len(layout)])
+    H = 6
+    lengths = scene(layout, np.array([5, 1, 70, 0, 33, 2, 1, 2, 1, 300]))
+    ids = workloads.ids_from_lengths(lengths, rng)
+    n, W = ids.size, lengths.size
+    q, k, v, do = (workloads.normal_values(rng, n, H, d, dtype) for _ in range(4))
+    # (zero columns in the first ten windows only: of a gradient through a floored norm fp32
+    # leaves 2^-24 of its terms / 1e-12, some 1e4, so that among many the rare one below
+    # fp16's range would be all rounding; in the others it is infinite on both sides)
+    first = ids < 10
+    q[first, 1, 7] = 0
+    k[first, 2, d - 2] = 0
+    small = np.isin(ids, np.flatnonzero(lengths[:10] <= 2))
+    for x in (q, k):
+        x32 = oracle.widen(x, dtype)
+        x32[small, 3, :] *= 1e-3
+        x[...] = workloads.cast_values(x32.astype(np.float32), dtype)
+    label = f"degenerate {layout} d{d}"
+    xca_parity(sla, ids, None, n, W, q, k, v, np.array([0.0, 40.0, 1.0, -3.0, 0.5, 2.0]), dtype, label=label)
+    xca_backward_parity(sla, ids, None, n, W, q, k, v, do, np.array([0.0, 2.0, 1.0, -3.0, 0.5, 2.0]), dtype, label=label)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("d", [16, 32])
+def test_thin_windows_on_items(sla, d, dtype):  # noqa: F811
+    # many slots, few of them with a row or three: work items whose chunks span pages of 64
+    # slots and are split into parts
+    rng = np.random.default_rng([96, d, len(dtype)])
+    lengths = (rng.random(4000) < 0.1) * rng.integers(1, 4, size=4000)
+    ids = workloads.ids_from_lengths(lengths.astype(np.int64), rng)
+    n, W, H = ids.size, lengths.size, 2
+    q, k, v, do = (workloads.normal_values(rng, n, H, d, dtype) for _ in range(4))
+    tau = np.array([-1.5, 4.0])
+    xca_parity(sla, ids, None, n, W, q, k, v, tau, dtype, label=f"thin d{d}")
+    xca_backward_parity(sla, ids, None, n, W, q, k, v, do, tau, dtype, label=f"thin d{d}")
