@@ -303,7 +303,10 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
         Raw<T, 8> xj[2][CB];
         xjob_fetch<T, CB>(xj, bk.j[jj].o, bk.j[jj].ok, cur.br, jj, ww.ra, ww.rb, n, x, g);
         project_job<T, D, CB>(bk.j[jj], xj, kAll, s_w, s_b, i, g);
-        if constexpr (SAVE) save_job<T, D>(bk.j[jj], kAll, qkv, nC, rs, col, g);
+        // of a chunk's parts the one whose windows hold a job's first row saves it (every
+        // part that reaches a job projects all of it)
+        if constexpr (SAVE)
+          if (!PARTS || fa <= r0) save_job<T, D>(bk.j[jj], kAll, qkv, nC, rs, col, g);
         __builtin_amdgcn_sched_barrier(0);
       }
       for (bool more = wi.first(ww, cur.str); more; more = wi.next(ww, cur.str)) {

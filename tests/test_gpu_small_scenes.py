@@ -100,20 +100,21 @@ def test_builder_either_side_of_the_totals(sla, n, W):  # noqa: F811
     check_plan(sla, plan, ids, W, 0)
 
 
-@pytest.mark.parametrize("rows", [60, 2003, 70001])
+@pytest.mark.parametrize("rows,per", [(60, 37), (2003, 37), (70001, 37), (500, 3), (3001, 5)])
 @pytest.mark.parametrize("H,d", [(2, 32), (8, 32)])
-def test_saved_qkv_beside_idle_waves(sla, rows, H, d):  # noqa: F811
+def test_saved_qkv_beside_idle_waves(sla, rows, per, H, d):  # noqa: F811
     # the last chunk items leave waves without rows: with parts (few rows) and without
     # (many), they store nothing into the saved q, k, v; rows of no window keep what
-    # the buffer held, the others hold the projection
+    # the buffer held, the others hold the projection; windows of a few rows: a job that
+    # several parts project is saved by one of them
     import torch
     from tests.gpu_util import to_dev
 
     rng = np.random.default_rng([73, rows, H, d])
-    ids = rng.integers(0, max(1, rows // 37), size=rows).astype(np.int32)
+    ids = rng.integers(0, max(1, rows // per), size=rows).astype(np.int32)
     ids[rng.random(rows) < 0.02] = -1
     C = H * d
-    plan = sla.build_segments(to_dev(ids), num_windows=max(1, rows // 37))
+    plan = sla.build_segments(to_dev(ids), num_windows=max(1, rows // per))
     gen = torch.Generator(device="cuda").manual_seed(73)
     rand = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
     x, wq, bq = (t.bfloat16() for t in (rand(rows, C), rand(3 * C, C) / C**0.5, 1.0 + rand(3 * C)))
