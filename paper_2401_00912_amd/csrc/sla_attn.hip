@@ -318,8 +318,8 @@ static hipError_t fwd_impl(const void* plan, int32_t n, int32_t W, int32_t H, fl
                            hipStream_t stream) {
   const PlanLayout lay = plan_layout(n, W);
   const KernelArgs a = kernel_args(plan, lay, n, W, H, eps);
-  const int grid = grid_size(reinterpret_cast<const void*>(&k_sla_fwd<T, D, PHI, false>), lay, n, H);
-  const auto kern = parts_fit(grid, n, W, H, kPartFill) ? &k_sla_fwd<T, D, PHI, true> : &k_sla_fwd<T, D, PHI, false>;
+  int grid;
+  const auto kern = pick_parts(&k_sla_fwd<T, D, PHI, false>, &k_sla_fwd<T, D, PHI, true>, lay, n, W, H, kPartFill, grid);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a, static_cast<const T*>(q),
                      static_cast<const T*>(k), static_cast<const T*>(v), static_cast<T*>(o));
   return hipGetLastError();
@@ -331,8 +331,8 @@ static hipError_t bwd_impl(const void* plan, int32_t n, int32_t W, int32_t H, fl
                            void* dk, void* dv, hipStream_t stream) {
   const PlanLayout lay = plan_layout(n, W);
   const KernelArgs a = kernel_args(plan, lay, n, W, H, eps);
-  const int grid = grid_size(reinterpret_cast<const void*>(&k_sla_bwd<T, D, PHI, false>), lay, n, H);
-  const auto kern = parts_fit(grid, n, W, H, kPartFill) ? &k_sla_bwd<T, D, PHI, true> : &k_sla_bwd<T, D, PHI, false>;
+  int grid;
+  const auto kern = pick_parts(&k_sla_bwd<T, D, PHI, false>, &k_sla_bwd<T, D, PHI, true>, lay, n, W, H, kPartFill, grid);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a, static_cast<const T*>(q), static_cast<const T*>(k),
                      static_cast<const T*>(v), static_cast<const T*>(dout), static_cast<T*>(dq),
                      static_cast<T*>(dk), static_cast<T*>(dv));

@@ -1331,6 +1331,15 @@ inline int grid_size(const void* kernel, const PlanLayout& lay, int32_t n, int32
   return (int)(g < 8 ? 8 : g);
 }
 
+// The kernel with or without parts, and the grid of the one that runs.
+template <class K>
+K* pick_parts(K* plain, K* parts, const PlanLayout& lay, int32_t n, int32_t W, int32_t H, int fill, int& grid) {
+  grid = grid_size(reinterpret_cast<const void*>(plain), lay, n, H);
+  if (!parts_fit(grid, n, W, H, fill)) return plain;
+  grid = grid_size(reinterpret_cast<const void*>(parts), lay, n, H);
+  return parts;
+}
+
 inline KernelArgs kernel_args(const void* plan, const PlanLayout& lay, int32_t n, int32_t W,
                               int32_t H, float eps) {
   const char* base = static_cast<const char*>(plan);

@@ -121,17 +121,32 @@ __host__ __device__ __forceinline__ Slot item_slot(const Items& it, int32_t item
   return sl;
 }
 
-// Whether a launch of `grid` workgroups may find its chunks too few for it (a chunk
-// holds fewer than kMaxChunkRows rows), so that parts are worth their code: the
-// kernels without them, one to two percent faster on larger scenes, run otherwise.
-// work_items allows as many parts as window slots, so that two parts a chunk need
-// at most half as many chunks, n / kMaxChunkRows of them or more, as slots; or
-// twice that where they fill an eighth of the grid.
+// Rows of a chunk, as the host guesses their number before the plan is there: windows of up
+// to 32 rows share one when they start in the same 32 rows of the sorted order, so a scene of
+// thin windows has chunks of 32 to 35 rows (frames of 6k to 16k rows in 900 to 3,481
+// windows), one of 60k rows in 1,521 windows 62.
+constexpr int32_t kThinChunkRows = 36;
+
+// Whether a launch of `grid` workgroups will split its chunks into parts, by that guess and
+// the rule of make_items.  The kernels without parts, two to four percent faster where
+// nothing is split, run otherwise.
 inline bool parts_fit(int grid, int32_t n, int32_t W, int32_t H, int fill) {
-  const int hw = H < 4 ? H : 4, cpw = 4 / hw, hg = (H + 3) / 4;
-  const int64_t items = (int64_t)n * hg * 2, room = (int64_t)grid * kMaxChunkRows * cpw;   // x kMaxChunkRows cpw
-  if ((int64_t)n * 2 > (int64_t)W * kMaxChunkRows && items * 8 > room) return false;
-  return items * 100 <= room * fill;
+  const int32_t chunks = (n + kThinChunkRows - 1) / kThinChunkRows;
+  return make_items(0, 0, chunks < W ? chunks : W, H, W, grid, fill, 1).part_bits > 0;
+}
+
+// The same for the fused projection: nC chunks, four to a workgroup of every head, split into
+// 2^bits parts that fill the grid at most once.
+__host__ __device__ __forceinline__ int proj_part_bits(int32_t nC, int32_t H, int32_t W, int32_t grid) {
+  const int64_t groups = ((int64_t)nC + 3) / 4;
+  int bits = 0;
+  while (bits < kMaxPartBits && ((int64_t)nC << (bits + 1)) <= W && (groups << (bits + 1)) * H <= grid) ++bits;
+  return bits;
+}
+
+inline bool proj_parts_fit(int grid, int32_t n, int32_t W, int32_t H) {
+  const int32_t chunks = (n + kThinChunkRows - 1) / kThinChunkRows;
+  return proj_part_bits(chunks < W ? chunks : W, H, W, grid) > 0;
 }
 
 }  // namespace sla

@@ -58,10 +58,7 @@ __device__ __forceinline__ ProjItems proj_items(const KernelArgs& a, const PlanH
   it.H = a.H;
   it.itemsL4 = ((it.nL4 + 7) & ~7) * a.H;
   it.itemsL = it.itemsL4 + ((it.nL2p + 7) & ~7) * a.H;
-  it.part_bits = 0;
-  while (PARTS && it.part_bits < kMaxPartBits && (it.nC << (it.part_bits + 1)) <= a.W &&
-         ((int64_t)it.nCG << (it.part_bits + 1)) * a.H <= (int64_t)gridDim.x)
-    ++it.part_bits;
+  it.part_bits = PARTS ? proj_part_bits(it.nC, a.H, a.W, (int32_t)gridDim.x) : 0;
   it.total = it.itemsL + (((it.nCG << it.part_bits) + 7) & ~7) * a.H;
   return it;
 }
@@ -460,24 +457,30 @@ static hipError_t proj_impl(const void* plan, int32_t n, int32_t W, int32_t H, f
                             const void* bo, void* o, void* y, void* qkv, hipStream_t stream) {
   const PlanLayout lay = plan_layout(n, W);
   const KernelArgs a = kernel_args(plan, lay, n, W, H, eps);
-  void (*fk)(KernelArgs, ProjArgs, T*) =
-      qkv ? &k_sla_fwd_proj<T, D, PHI, CB, true, false> : &k_sla_fwd_proj<T, D, PHI, CB, false, false>;
-  const void* kern = reinterpret_cast<const void*>(fk);
-  const int64_t c = resident_workgroups(kern);
+  using Kernel = void(KernelArgs, ProjArgs, T*);
   const int64_t unit = 8 * (int64_t)H;
   const int64_t ml = lay.max_long, mc = lay.max_chunks;
-  int64_t items = (((ml + 7) & ~7) + (((ml + 1) / 2 + 7) & ~7) + (((mc + 3) / 4 + 7) & ~7)) * H;
-  int64_t k = ((int64_t)n * H + c * kRowHeadsPerWorkgroup / 2) / (c * kRowHeadsPerWorkgroup);
-  if (k < 1) k = 1;
-  int64_t g = k * c;
-  // few chunks (fewer than kMaxChunkRows rows each) leave room for parts
-  if ((int64_t)n * 2 * H <= g * 4 * kMaxChunkRows) {
+  const auto grid_of = [&](Kernel* kern, int part_bits) {
+    const int64_t items =
+        (((ml + 7) & ~7) + (((ml + 1) / 2 + 7) & ~7) + ((((mc + 3) / 4 << part_bits) + 7) & ~7)) * H;
+    const int64_t c = resident_workgroups(reinterpret_cast<const void*>(kern));
+    int64_t k = ((int64_t)n * H + c * kRowHeadsPerWorkgroup / 2) / (c * kRowHeadsPerWorkgroup);
+    if (k < 1) k = 1;
+    int64_t g = k * c;
+    if (g > items) g = items;
+    g = (g + unit - 1) / unit * unit;
+    return g < unit ? unit : g;
+  };
+  // the kernel with or without parts, and the grid of the one that runs (they may differ in
+  // their registers: fp16, C = 128, saving q, k, v, 157 VGPRs without and 191 with parts; a
+  // grid for three workgroups per CU run with two took 28.5 us instead of 23.1 on 6k rows in
+  // 900 windows)
+  Kernel* fk = qkv ? &k_sla_fwd_proj<T, D, PHI, CB, true, false> : &k_sla_fwd_proj<T, D, PHI, CB, false, false>;
+  int64_t g = grid_of(fk, 0);
+  if (proj_parts_fit((int)g, n, W, H)) {
     fk = qkv ? &k_sla_fwd_proj<T, D, PHI, CB, true, true> : &k_sla_fwd_proj<T, D, PHI, CB, false, true>;
-    items <<= kMaxPartBits;
+    g = grid_of(fk, kMaxPartBits);
   }
-  if (g > items) g = items;
-  g = (g + unit - 1) / unit * unit;
-  if (g < unit) g = unit;
   const ProjArgs pa{x, wqkv, bqkv, qkv};
   hipLaunchKernelGGL(fk, dim3((unsigned)g), dim3(64 * kWaves), 0, stream, a, pa, static_cast<T*>(o));
   hipError_t e = hipGetLastError();

@@ -278,8 +278,8 @@ hipError_t xca_impl(const void* plan, int32_t n, int32_t W, int32_t H, const flo
                                     stream);
   const PlanLayout lay = plan_layout(n, W);
   const KernelArgs a = kernel_args(plan, lay, n, W, H, 0.f);
-  const int grid = grid_size(reinterpret_cast<const void*>(&k_xca_fwd_mma<T, D, false>), lay, n, H);
-  const auto kern = parts_fit(grid, n, W, H, kXcaFwdFill) ? &k_xca_fwd_mma<T, D, true> : &k_xca_fwd_mma<T, D, false>;
+  int grid;
+  const auto kern = pick_parts(&k_xca_fwd_mma<T, D, false>, &k_xca_fwd_mma<T, D, true>, lay, n, W, H, kXcaFwdFill, grid);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a, tau, qt, kt, vt, static_cast<T*>(o));
   return hipGetLastError();
 }
@@ -300,9 +300,9 @@ hipError_t xca_bwd_impl(const void* plan, int32_t n, int32_t W, int32_t H, const
       e = launch_xca_win_bwd<T, D>(plan, n, W, H, path == XcaPath::kWinLong, tau, qt, kt, vt, dt, dqt, dkt, dvt, part,
                                    stream);
     } else {
-      const int grid = grid_size(reinterpret_cast<const void*>(&k_xca_bwd_mma<T, D, false>), lay, n, H);
+      int grid;
       const auto kern =
-          parts_fit(grid, n, W, H, kXcaBwdFill) ? &k_xca_bwd_mma<T, D, true> : &k_xca_bwd_mma<T, D, false>;
+          pick_parts(&k_xca_bwd_mma<T, D, false>, &k_xca_bwd_mma<T, D, true>, lay, n, W, H, kXcaBwdFill, grid);
       hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), 0, stream, a, tau, qt, kt, vt, dt, dqt, dkt, dvt, part);
       e = hipGetLastError();
     }

@@ -95,3 +95,40 @@ def test_launch_table_is_safe_with_threads(gxx):
     # (address randomisation off: the sanitizer's shadow needs the low mappings free)
     res = gxx(TABLE, "-g", "-pthread", "-fsanitize=thread", wrap=["setarch", "-R"])
     assert res.returncode == 0, (res.returncode, res.stdout, res.stderr[-2000:])
+
+
+PARTS = r"""
+#include "sla_items.h"
+#include <cstdio>
+using namespace sla;
+int main() {
+  // where the host takes the kernels with parts, the device splits the chunks of a scene of
+  // the guessed size, and nowhere else; parts fill the grid as far as they may
+  const int heads[] = {1, 2, 3, 4, 6, 8, 12}, windows[] = {38, 169, 900, 1521, 3481}, grids[] = {512, 768, 1536};
+  const int fills[] = {100, 200, 400};
+  int with = 0, without = 0;
+  for (int H : heads) for (int W : windows) for (int grid : grids)
+  for (int n = 50; n < 300000; n = n * 5 / 4) {
+    int nC = (n + kThinChunkRows - 1) / kThinChunkRows;
+    if (nC > W) nC = W;
+    for (int fill : fills) {
+      const Items it = make_items(0, 0, nC, H, W, grid, fill, kMaxPartBits);
+      if ((it.part_bits > 0) != parts_fit(grid, n, W, H, fill)) return 1;
+      if (it.part_bits > 0 && it.total > fill * (long)grid / 100) return 2;
+    }
+    const int bits = proj_part_bits(nC, H, W, grid);
+    if ((bits > 0) != proj_parts_fit(grid, n, W, H)) return 3;
+    if (bits > 0 && (((long)(nC + 3) / 4) << bits) * H > grid) return 4;
+    if (bits > 0 && ((long)nC << bits) > W) return 5;
+    ++(bits > 0 ? with : without);
+  }
+  // 16k rows in 3,481 windows, 8 heads: 498 chunks fill the projection's grid without parts
+  if (proj_parts_fit(512, 16001, 3481, 4)) return 6;
+  return with > 50 && without > 50 ? 0 : 7;
+}
+"""
+
+
+def test_parts_where_the_device_splits(gxx):
+    res = gxx(PARTS)
+    assert res.returncode == 0, res.returncode
