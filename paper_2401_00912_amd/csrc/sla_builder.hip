@@ -801,9 +801,15 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(
 //    3,042    15.3 / 16.1  16.9 / 17.0  18.1 / 17.8  21.5 / 18.9  24.1 / 17.8
 //    3,481    17.0 / 16.9  18.7 / 18.1  20.5 / 19.2  24.3 / 19.9  26.7 / 19.0
 //    6,084    20.0 / 19.4  22.2 / 21.0  24.3 / 22.4  28.2 / 23.2  30.7 / 23.0
-// at 10k rows 14.8 / 15.8 in 3,481 windows and 18.3 / 18.1 in 6,084; 480k rows in 256
-// (120k counts) 21.9 / 22.9; 1M in 2,000 70.0 / 46.7.
+// at 10k rows 14.8 / 15.8 in 3,481 windows and 18.3 / 18.1 in 6,084; 1M in 2,000 70.0 / 46.7.
+// Up to 1,024 totals k_sort adds in one pass (1,156 windows cost what 1,521 do), and the
+// line lies with the rows:
+//   windows   160k rows    200k rows    300k rows    480k rows    1M rows
+//      64    13.2 / 13.4  15.4 / 15.4  19.3 / 19.1  27.4 / 25.9  51.1 / 44.3
+//     256    13.1 / 15.0  14.1 / 16.2  18.0 / 20.4  22.1 / 21.9  40.1 / 35.5
+//     900    14.0 / 16.0  14.8 / 17.1  18.9 / 20.2  25.5 / 25.1  46.7 / 41.1
 static bool use_totals(int64_t n, int64_t n_blocks, int64_t W) {
+  if (W < kSortThreads) return n <= 440000;
   const int64_t counts = std::min(n, n_blocks * W);
   return counts <= (W <= 2048 ? 130000 : (W <= 3200 ? 75000 : (W <= 5000 ? 40000 : 10000)));
 }

@@ -81,7 +81,7 @@ def one_row_backward(S, ids, W, q, k, v, do, dtype):
 
 @pytest.mark.parametrize("n,W", [(60000, 2049), (60001, 2049), (160000, 2048), (160001, 2048), (160001, 7), (130000, 2048),
                                  (130001, 2048), (75000, 2049), (75001, 2049), (40000, 3201), (40001, 3201),
-                                 (10000, 5001), (10001, 5001)])
+                                 (10000, 5001), (10001, 5001), (440000, 1023), (440001, 1023), (130001, 1024)])
 def test_builder_either_side_of_the_totals(sla, n, W):  # noqa: F811
     # the builder sums its window counts with atomics up to a number of counts, and over
     # the blocks' prefix rows above it: out-of-range ids, long windows and empty ones on
