@@ -9,8 +9,8 @@
 //
 // Neighbours are found through a dense cell -> row table of the grid (for the
 // 468 x 468 pillar grid 0.9 MB), built per scene by k_cwi_clear + k_cwi_map.
-// The work is a gather, bound by memory latency and bandwidth, not a contraction:
-// no matrix cores.  A wave takes one branch of a group of rows (so no wave runs
+// The work is a gather, bound by memory latency and bandwidth, not a contraction (the
+// kernel gradients in 16 bits still use the matrix cores: k_cwi_dw_mma).  A wave takes one branch of a group of rows (so no wave runs
 // two branches' loops); lane (row, piece) owns 16 bytes of the row's channels of
 // that branch.  Taps go in groups of eight: the table entries of the group are
 // requested together, then the neighbour pieces and weights, then the fp32
@@ -566,26 +566,6 @@ hipError_t launch_cwi_forward(const int32_t* map, int32_t gx, int32_t gy, int32_
                             w_3, y, stream, 0);
 }
 
-// ------------------------------------------------------------------ backward
-// The chain rule of the module, per tap: dx[q] += w[t] dy[p] and
-// dw[t] += dy[p] x[q] for the voxel q at p's cell + offset_t.
-//  * dx: with unique voxels, q is p's neighbour at +o exactly when p is q's at -o,
-//    so dx is the forward applied to dy with every kernel reversed (flip); the
-//    identity quarter passes dy through.
-//  * dw, fp32 (16-bit storage: k_cwi_dw_mma below): k_cwi_dw.  A lane owns one (tap, 16-byte piece) pair of a branch, so
-//    its fp32 sums are one piece (4 channels) and no sums are
-//    exchanged between lanes: a wave covers 64 pairs (the 13 taps x 4 pieces
-//    of a 32-channel fp16 branch fit one wave) and walks a contiguous range of
-//    rows, kDwBatch rows at a time with all their loads in flight (a row's
-//    index and cell are the same for the whole wave: fetched once per 64 rows,
-//    one per lane, and broadcast with readlane).  The four waves of a
-//    workgroup take adjacent row ranges; their sums are added in wave order
-//    and written as the workgroup's partial, and k_cwi_dw_reduce adds the
-//    partials in workgroup order.  Every order is fixed, so the result is
-//    deterministic.  XCD placement: the row blocks of a (branch, slice) are a
-//    multiple of 8 and workgroup j of it takes row block (j mod 8) B / 8 + j / 8
-//    (B blocks), so each XCD walks one contiguous eighth of the rows for every
-//    branch and slice, and its L2 serves the lines they share.
 // Nonzero when a 16-byte piece of 16-bit values holds an infinity or NaN: adding one
 // to an exponent field of all ones carries into the sign's place.
 template <typename T>
@@ -602,6 +582,26 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+// ------------------------------------------------------------------ backward
+// The chain rule of the module, per tap: dx[q] += w[t] dy[p] and
+// dw[t] += dy[p] x[q] for the voxel q at p's cell + offset_t.
+//  * dx: with unique voxels, q is p's neighbour at +o exactly when p is q's at -o,
+//    so dx is the forward applied to dy with every kernel reversed (flip); the
+//    identity quarter passes dy through.
+//  * dw: k_cwi_dw (most 16-bit calls: k_cwi_dw_mma below).  A lane owns one (tap, 16-byte
+//    piece) pair of a branch, so its fp32 sums are one piece (8 fp16 or 4 fp32 channels)
+//    and no sums are exchanged between lanes: a wave covers 64 pairs (the 13 taps x 4 pieces
+//    of a 32-channel fp16 branch fit one wave) and walks a contiguous range of
+//    rows, kDwBatch rows at a time with all their loads in flight (a row's
+//    index and cell are the same for the whole wave: fetched once per 64 rows,
+//    one per lane, and broadcast with readlane).  The four waves of a
+//    workgroup take adjacent row ranges; their sums are added in wave order
+//    and written as the workgroup's partial, and k_cwi_dw_reduce adds the
+//    partials in workgroup order.  Every order is fixed, so the result is
+//    deterministic.  XCD placement: the row blocks of a (branch, slice) are a
+//    multiple of 8 and workgroup j of it takes row block (j mod 8) B / 8 + j / 8
+//    (B blocks), so each XCD walks one contiguous eighth of the rows for every
+//    branch and slice, and its L2 serves the lines they share.
 constexpr int kDwWaves = 4;          // waves per workgroup: adjacent row ranges
 constexpr int kDwBatch = 8;          // rows whose loads are in flight together
 #ifndef SLA_CWI_DW_ROWS
@@ -975,20 +975,48 @@ size_t cwi_backward_workspace_bytes(int32_t n, int32_t channels, int32_t kx, int
   return (size_t)g.blocks * (size_t)((kx + ky + 27) * c) * sizeof(float);
 }
 
+// 16-bit storage: whether k_cwi_dw_mma forms the kernel gradients, or k_cwi_dw.  The products
+// save reads of dy and idle lanes, and cost LDS round trips; where the rows come from HBM
+// anyway k_cwi_dw, whose lanes read wider rows, is the faster one, in bf16, whose
+// conversions it pays per tap, only with few taps.  Backward, us, products against k_cwi_dw:
+//   grid 8 deep                    fp16            bf16
+//     C = 128, 13 taps, 500 rows  18.3 / 17.7     19.0 / 18.5
+//       2k rows                   26.9 / 27.6     27.7 / 29.1
+//       30k rows                  42.4 / 42.9     44.4 / 48.8
+//       60k rows                  68.0 / 64.4     71.0 / 73.7
+//     C = 256, 30k rows           67.2 / 63.2     72.0 / 72.4
+//       3 taps                    61.8 / 54.5     64.0 / 60.4
+//     C = 512, 30k rows            115 / 107       120 / 124
+//   pillars
+//     C = 256, 60k rows           73.3 / 72.9     79.2 / 88.3
+//     C = 512, 60k rows            137 / 126       148 / 153
+//     C = 1,024, 12k rows         99.9 / 92.4      109 / 107
+static bool dw_by_products(const CwiArgs& a, bool f16) {
+  const int64_t elems = (int64_t)a.n * 4 * a.c;
+  if (a.gz == 1) return !(f16 && a.pq >= 16 && elems >= 12000000);
+  if (a.pq >= 4 && a.n < 1000) return false;
+  return elems < 7000000 || (!f16 && a.kx + a.ky > 12);
+}
+
 template <typename T>
 static hipError_t launch_dw(const CwiArgs& a, const DwGrid& g, const void* x, const void* dy,
                             float* partial, void* dw_x, void* dw_y, void* dw_3, hipStream_t stream) {
   const T *xs = static_cast<const T*>(x), *ds = static_cast<const T*>(dy);
   int32_t blocks = g.blocks;
-  if constexpr (std::is_same<T, float>::value) {
+  bool products = false;
+  if constexpr (!std::is_same<T, float>::value) {
+    products = dw_by_products(a, std::is_same<T, _Float16>::value);
+    if (products) {
+      const DwGrid m = cwi_dw_mma_grid(a.n, a.c, a.kx, a.ky, a.gz);
+      const auto kern = a.pq >= 4 ? &k_cwi_dw_mma<T, 4> : (a.pq == 2 ? &k_cwi_dw_mma<T, 2> : &k_cwi_dw_mma<T, 1>);
+      const unsigned grid = (unsigned)((m.slices[0] + m.slices[1] + m.slices[2]) * m.blocks);
+      hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, a, m, xs, ds, partial);
+      blocks = m.blocks;
+    }
+  }
+  if (!products) {
     const unsigned grid = (unsigned)((g.slices[0] + g.slices[1] + g.slices[2]) * g.blocks);
     hipLaunchKernelGGL((k_cwi_dw<T>), dim3(grid), dim3(256), 0, stream, a, g, xs, ds, partial);
-  } else {
-    const DwGrid m = cwi_dw_mma_grid(a.n, a.c, a.kx, a.ky, a.gz);
-    const auto kern = a.pq >= 4 ? &k_cwi_dw_mma<T, 4> : (a.pq == 2 ? &k_cwi_dw_mma<T, 2> : &k_cwi_dw_mma<T, 1>);
-    const unsigned grid = (unsigned)((m.slices[0] + m.slices[1] + m.slices[2]) * m.blocks);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, a, m, xs, ds, partial);
-    blocks = m.blocks;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -13,7 +13,8 @@ from tests.test_gpu_parity import sla  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("C,kx,ky,n,gz", [(32, 3, 17, 33, 2), (64, 13, 13, 700, 3), (128, 5, 1, 300, 1), (256, 3, 3, 64, 1)])
+@pytest.mark.parametrize("C,kx,ky,n,gz", [(32, 3, 17, 33, 2), (64, 13, 13, 700, 3), (128, 5, 1, 300, 1), (256, 3, 3, 64, 1),
+                                          (128, 3, 5, 500, 3)])   # the last: k_cwi_dw
 def test_dw_not_finite(sla, C, kx, ky, n, gz):  # noqa: F811
     import torch
 
