@@ -29,10 +29,13 @@ namespace sla {
 constexpr int kProjMaxC = 256;
 // A block's features are fetched and projected one 32-row job at a time, so that
 // at most one job's features are live (8 VGPRs per 32 channels).  Both jobs' at once
-// took the bf16 kernels over 256 VGPRs and spilled 14 to 34 of them: 60k rows, C =
-// 128, with the output projection, 45.2 us against 50.7 at d = 32 and 48.4 against
-// 56.5 at d = 16; fp16, which did not spill, 43.0 against 43.4, and 47.8 against 46.5
-// with seven input sets in turn, all from HBM.
+// take the bf16 kernels over 256 VGPRs, and they spill 14 to 34 of them: 60k rows, C =
+// 128, with the output projection, 45.2 us job by job against 50.7 at d = 32 and 48.4
+// against 56.5 at d = 16.  fp16 at C = 128, d = 32 does not spill and, without a store per
+// job or parts, keeps both in flight: 60k rows 46.6 us against 47.4 job by job, 100k rows
+// 71.5 against 73.4, inputs from HBM.
+template <typename T, int D, int CB, bool SAVE, bool PARTS>
+constexpr bool kBothJobs = std::is_same<T, _Float16>::value && D == 32 && CB == 4 && !SAVE && !PARTS;
 
 struct ProjArgs {
   const void* x;  // [n, C] features
@@ -178,6 +181,14 @@ __device__ __forceinline__ void xjob_fetch(Raw<T, 8> (&xj)[2][CB], int32_t (&o)[
   }
 }
 
+// Both jobs' features of a block, all requested before the first is used.
+template <typename T, int CB>
+struct XBlock {
+  Raw<T, 8> x[kBlockJobs][2][CB];
+  int32_t o[kBlockJobs][2];
+  bool ok[kBlockJobs][2];
+};
+
 // One 32-row job of a share longer than a block (streamed): rows through the
 // permutation, features, and the selected matrices.
 template <typename T, int D, int CB>
@@ -270,11 +281,17 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
     const WaveWork ww = cur.ww;
     const int col = ww.h * D;
     const bool resident = ww.rb - ww.ra <= kBlockRows;
-    const unsigned first = resident ? kAll : kKV;
     // a share of more than kBlockRows rows (a quarter of a very long window) is
     // streamed job by job: K, V for the state, then Q for the outputs.  The two
     // cases are separate branches, each with its own window loop, so that the
     // resident rows are not live in the streamed one.
+    constexpr bool kBoth = kBothJobs<T, D, CB, SAVE, PARTS>;
+    XBlock<T, kBoth ? CB : 1> xb;
+    if constexpr (kBoth)
+      if (ww.kind != 0 && resident)
+#pragma unroll
+        for (int jj = 0; jj < kBlockJobs; ++jj)
+          xjob_fetch<T, CB>(xb.x[jj], xb.o[jj], xb.ok[jj], cur.br, jj, ww.ra, ww.rb, n, x, g);
     // the next item: its rows and windows are requested now, its successor's entry too
     Pending nxt;
     pending_request(nxt, a, nsl, ne, wv, perm, lane);
@@ -291,6 +308,19 @@ void k_sla_fwd_proj(KernelArgs a, ProjArgs pa, T* __restrict__ o) {
     }
     if (resident) {
       Block<T, D, 3> bk;
+      if constexpr (kBoth) {
+        if (ww.kind != 0)   // (job by job the row list of an idle wave is empty)
+#pragma unroll
+          for (int jj = 0; jj < kBlockJobs; ++jj) {
+            project_job<T, D, CB>(bk.j[jj], xb.x[jj], kAll, s_w, s_b, i, g);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+              bk.j[jj].ok[s] = xb.ok[jj][s];
+              bk.j[jj].o[s] = xb.o[jj][s];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+      } else
 #pragma unroll
       for (int jj = 0; jj < kBlockJobs; ++jj) {
         [[maybe_unused]] const int32_t r0 = ww.ra + kSliceRows * jj;
