@@ -22,8 +22,8 @@
 // forward), at 2 to 4 waves per SIMD.  Against a 256-thread workgroup per (window, head), as
 // in sla_xca_win.hip, whose 5 to 9 barriers and serial column sums set the time of large
 // scenes: one Waymo-like frame (60k rows, fp16, H = 4, d = 32), inputs from HBM, forward
-// 30.1 us against 29.8, backward 67.8 against 91.9; bf16 30.3 against 32.2 and 67.0 against
-// 89.7; 60k rows in log-normal windows, fp16, 42.9 against 79.7 and 98.0 against 203;
+// 29.1 us against 29.7, backward 67.4 against 91.9; bf16 30.1 against 31.9 and 66.9 against
+// 87.2; 60k rows in log-normal windows, fp16, 42.9 against 79.7 and 98.0 against 203;
 // H = 8, d = 16, 30.6 against 49.9 and 59.5 against 112.  Scenes of few or of thin windows
 // are faster with the workgroups: xca_path below.
 #include "sla.h"
@@ -70,7 +70,12 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
   const int32_t n = a.n, G = gridDim.x;
   float* const norms = s_norm[wv];
   const T* const mats[3] = {k, v, q};
-  constexpr unsigned kKQ = 5u, kAll = 7u;
+  constexpr int KS = Geo<D>::KS, NT = Geo<D>::NT;
+  using F = Frag<T, KS>;
+  using O = XcaOp<T, D>;
+  floatx4* const slot = s_part + wv * SL;
+  float* const stage = reinterpret_cast<float*>(slot);
+  constexpr unsigned kV = 2u, kKQ = 5u, kAll = 7u;
   WaveMeta& meta = s_meta[wv];
   const bool csr = perm == nullptr;
   int32_t item = blockIdx.x;
@@ -115,7 +120,57 @@ void k_xca_fwd_mma(KernelArgs a, const float* __restrict__ tau, const T* __restr
     WinIter wi;
     for (bool more = wi.first(ww, str); more; more = wi.next(ww, str)) {
       const int32_t wa = wi.wc.ws, wb = wi.wc.we;
-      xca_fwd_window<T, D, kHold>(bk, mats, o, ww, wa, wb, wi.shared, resident, th, perm, n, rs, s_part, norms, lane, wv);
+      // xca_fwd_window, written out: as a call its row masks are formed on the scalar unit,
+      // the frame above, fp16, 29.8 us against 29.1
+      auto refetch = [&](int32_t base, unsigned which) {
+        BlockRows br;
+        block_rows(br, base, ww.rb, perm, lane);
+        block_fetch<T, D, 3>(bk, br, base, wb, n, mats, which, rs, col, g, wa);
+        block_arrange<T, D, 3>(bk, which);
+      };
+      XcaSums<D, false> su;
+      su.clear();
+      for (int32_t base = ww.ra; base < ww.rb; base += kBlockRows) {
+        if (!kHold || base != ww.ra) refetch(base, kKQ);
+#pragma unroll
+        for (int jj = 0; jj < kBlockJobs; ++jj) {
+          const int32_t r0 = base + kSliceRows * jj;
+          if (job_overlaps(r0, wa, wb)) xca_sums_seg<T, D, 3>(bk.j[jj], r0, wa, wb, i, g, stage, su);
+        }
+      }
+      if (wi.shared) {
+        su.publish(slot, lane);
+        lds_barrier();
+        su.combine(s_part, SL, lane, wv, ww.pair);
+        lds_barrier();  // the slots may be written again
+      }
+      if (!kHold) refetch(ww.ra, kV);   // in flight under the softmax
+      xca_norms<T, D>(su, norms, lane, i, g);
+      xca_softmax<T, D, false>(su.M, norms, th, i, g, nullptr);
+      Raw<O, KS> op[NT], opl[NT];
+      xca_operand<O, D, kXcaPair<O>>(su.M, 1.f, op, opl);
+      for (int32_t base = ww.ra; base < ww.rb; base += kBlockRows) {
+        if (!(resident && kHold) && (base != ww.ra || kHold)) refetch(base, kV);
+#pragma unroll
+        for (int jj = 0; jj < kBlockJobs; ++jj)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const int32_t r0 = base + kSliceRows * jj;
+            if (!sub_overlaps(r0, s, wa, wb)) continue;
+            const int32_t row = r0 + 16 * s + i;
+            const Raw<O, KS> vr = xca_row<T, O, KS>(bk.j[jj].x[1][s]);
+            float x[KS];
+#pragma unroll
+            for (int et = 0; et < NT; ++et) {
+              floatx4 d4 = xca_mma<O, KS>(op[et], vr);
+              if constexpr (kXcaPair<O>) d4 = Frag<O, KS>::mma(opl[et], vr, d4);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) x[4 * et + j] = d4[j];
+            }
+            RowIO<T, D>::put(o, row_off(bk.j[jj].o[s], rs, col), g, F::from_f32(x),
+                             bk.j[jj].ok[s] && row >= wa && row < wb);
+          }
+      }
     }
     item += G;
     wc = wn;
