@@ -135,7 +135,7 @@ def pmc_summary(fetch_csv, write_csv):
         "kernel      dispatches  FETCH_raw_B   WRITE_raw_B   fetch_scaled_B  write_scaled_B  traffic_scaled_B",
     ]
     for k in ("k_sort", "k_offsets", "k_merge", "k_plan", "k_sla_fwd", "k_sla_bwd", "k_cwi_clear", "k_cwi_map",
-              "k_cwi_tiled", "k_cwi_fwd", "k_cwi_dw", "k_cwi_dw_reduce", "copy"):
+              "k_cwi_tiled", "k_cwi_fwd", "k_cwi_dw_mma", "k_cwi_dw", "k_cwi_dw_reduce", "copy"):
         if k in f and k in w:
             fr, wr = f[k][0], w[k][0]
             lines.append(f"{k:<11} {f[k][1]:>10}  {fr:>12.0f}  {wr:>12.0f}  {fr / ff:>14.0f}  "
