@@ -341,6 +341,7 @@ __device__ __forceinline__ void xca_operand(const floatx4 (&M)[Geo<D>::NT][Geo<D
 // The rows [wa, wb) of a window of this wave (whole, or `shared`: its rows are this wave's
 // share and the sums are added to the other waves'): sums, A, outputs.  HOLD: bk holds the
 // item's first block (`resident`: all of it); otherwise every pass reads its rows.
+// (k_xca_fwd_mma has the same steps written out, for the reason given there.)
 template <typename T, int D, bool HOLD>
 __device__ __forceinline__ void xca_fwd_window(Block<T, D, 3>& bk, const T* const (&mats)[3], T* o, const WaveWork& ww,
                                                int32_t wa, int32_t wb, bool shared, bool resident, float th,
